@@ -9,18 +9,20 @@
 // its best predecessor, and a link needs both.  C9 refits every chain of two
 // or more segments with one inward Kalman pass over all its clusters.
 //
-//   k_merge_ranges  first track of each sector (tracks are in sector order)
-//   k_merge_match   one thread per segment a: the tracks of the two
+//   k_merge_prep    per sector: first track (tracks are in sector order),
+//                   neighbours, tracks sorted by tan(lambda) bin
+//   k_merge_match   one wave per segment a: the tracks of the two
 //                   neighbouring sectors; tan(lambda) and q/pT are invariants
 //                   of the rotation and the propagation, so their windows are
-//                   tested first; survivors are rotated and propagated in
-//                   double.  Best successor kept locally; best predecessor by
-//                   a 64-bit atomicMin of (score as float bits, a).
+//                   tested first; survivors are propagated in double.  Best
+//                   successor kept in the wave; best predecessor by a 64-bit
+//                   atomicMin of (score as float bits, a).
 //   k_merge_link    mutual best -> next[a]; predecessor flags
-//   k_merge_count   per chain head: segments and clusters (scans follow)
-//   k_merge_emit    per chain head: merged cluster list, and the refit (state
-//                   and covariance in double) or the C5 result of a single
-//                   segment
+//   k_merge_count   per chain head: clusters (scans follow)
+//   k_merge_heads   per chain head: record, segment offsets, list of refits
+//   k_merge_copy    merged cluster lists
+//   k_merge_refit   the refit of the chains of several segments (state and
+//                   covariance in double)
 #include "device_common.h"
 
 namespace tpc {
@@ -174,77 +176,162 @@ __device__ __forceinline__ int32_t neighbour(int32_t ph, int step) {
   return side * kSide + (i + step + kSide) % kSide;
 }
 
-__global__ void __launch_bounds__(kThreads) k_merge_init(DevPtrs d, MergeArgs m, uint32_t nt) {
-  const uint32_t a = blockIdx.x * kThreads + threadIdx.x;
-  if (a >= nt) return;
-  m.pred_key[a] = ~0ull;
-  m.has_pred[a] = 0u;
+// Tracks of a sector in ascending tan(lambda) bin (any order inside a bin), for the matching: (tan(lambda),
+// q/pT, z, track) per slot, slot range = the sector's track range.
+constexpr int kPrepThreads = 1024;
+constexpr int kTanBins = 256;
+// Bin of a tan(lambda): monotone, so the tracks within a window lie between the bins of its ends.
+__device__ __forceinline__ int tan_bin(double tl) {
+  const double u = (tl + 2.0) * 64.0;
+  return u > 0.0 ? (u < kTanBins - 1 ? (int)u : kTanBins - 1) : 0;
 }
 
-__global__ void __launch_bounds__(kThreads) k_merge_ranges(DevPtrs d, MergeArgs m) {
-  const uint32_t s = blockIdx.x * kThreads + threadIdx.x;
-  if (s > d.S) return;
-  // first track of sector s: lower bound of s in the sorted track sectors
-  uint32_t lo = 0, hi = n_tracks(d);
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi) / 2;
-    if (d.out_sector[mid] < s) lo = mid + 1; else hi = mid;
+// One workgroup per sector: its track range, its neighbours in the frame, the
+// cleared per-track words and the sector's slots of the sorted list (a
+// counting sort with the bins in LDS).
+__global__ void __launch_bounds__(kPrepThreads) k_merge_prep(DevPtrs d, MergeArgs m) {
+  __shared__ uint32_t hist[kTanBins + 1], wsum[kPrepThreads / kWave], range[2];
+  __shared__ int32_t nb[2];
+  const uint32_t s = blockIdx.x, tid = threadIdx.x;
+  for (uint32_t b = tid; b < (uint32_t)kTanBins; b += kPrepThreads) hist[b] = 0u;
+  if (tid < 2) {
+    // first track of sector s and of sector s + 1: lower bounds in the sorted track sectors
+    uint32_t lo = 0, hi = n_tracks(d);
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi) / 2;
+      if (d.out_sector[mid] < s + tid) lo = mid + 1; else hi = mid;
+    }
+    range[tid] = lo;
+    nb[tid] = INT32_MAX;
   }
-  m.sec_first[s] = lo;
-  if (s < d.S) {
-    // the run's sector holding each physical neighbour (-1 if absent from the frame)
-    const int32_t ph = m.phys[s];
-    for (int k = 0; k < 2; ++k) {
-      int32_t hit = -1;
-      if (ph >= 0) {
-        const int32_t want = neighbour(ph, k == 0 ? -1 : 1);
-        for (uint32_t q = 0; q < d.S; ++q)
-          if (m.phys[q] == want) { hit = (int32_t)q; break; }
-      }
-      m.nbr[2 * s + k] = hit;
+  __syncthreads();
+  const uint32_t t0 = range[0], t1 = range[1];
+  const int32_t ph = m.phys[s];
+  if (ph >= 0) {
+    // the frame's first sector that holds each physical neighbour
+    const int32_t dn = neighbour(ph, -1), up = neighbour(ph, 1);
+    for (uint32_t q = tid; q < d.S; q += kPrepThreads) {
+      const int32_t v = m.phys[q];
+      if (v == dn) atomicMin(&nb[0], (int32_t)q);
+      if (v == up) atomicMin(&nb[1], (int32_t)q);
     }
   }
+  for (uint32_t t = t0 + tid; t < t1; t += kPrepThreads) {
+    m.pred_key[t] = ~0ull;
+    m.has_pred[t] = 0u;
+    if (ph >= 0) atomicAdd(&hist[tan_bin(d.out_param[(size_t)t * 5 + 3])], 1u);
+  }
+  __syncthreads();
+  if (tid < 2) m.nbr[2 * s + tid] = nb[tid] == INT32_MAX ? -1 : nb[tid];
+  if (tid == 0) {
+    m.sec_first[s] = t0;
+    if (s + 1 == d.S) m.sec_first[d.S] = t1;
+    if (s == 0) d.hdr->merge_refits = 0u;
+  }
+  if (ph < 0) return;
+  block_scan_array(hist, kTanBins, wsum);
+  for (uint32_t t = t0 + tid; t < t1; t += kPrepThreads) {
+    const float* p = d.out_param + (size_t)t * 5;
+    const uint32_t at = t0 + atomicAdd(&hist[tan_bin(p[3])], 1u);
+    m.sorted[at] = make_float4(p[3], p[4], p[1], __uint_as_float(t));
+  }
 }
 
-__global__ void __launch_bounds__(kThreads) k_merge_match(DevPtrs d, MergeArgs m, KfConst k) {
-  const uint32_t nt = n_tracks(d);
-  const uint32_t a = blockIdx.x * kThreads + threadIdx.x;
+// Path length S(x) of track state (s1, kap) over dx, with sin phi held at +-smax beyond it: monotone in
+// dx, so its values at the innermost and outermost row bound the path to any row the track reaches.
+__device__ __forceinline__ double path_bound(double s1, double kap, double dx, double smax) {
+  const double s2 = fmin(smax, fmax(-smax, s1 + kap * dx));
+  if (s2 != s1 + kap * dx) dx = (s2 - s1) / kap;   // clamped, so kap != 0
+  const double c1 = sqrt((1.0 - s1) * (1.0 + s1)), c2 = sqrt((1.0 - s2) * (1.0 + s2));
+  const double dy = dx * ((s1 + s2) / (c1 + c2));
+  const double L = sqrt(dx * dx + dy * dy), u = fmin(1.0, fabs(0.5 * kap * L));
+  return (dx >= 0.0 ? L : -L) * asin_over_d(u);
+}
+
+// One wave per track a: its lanes test the tracks of the two neighbouring
+// sectors whose tan(lambda) bin can match.  Cheap float32 windows with slack
+// (tan(lambda), q/pT, and the z that a's path can reach) leave a few
+// candidates, which are tested exactly in double.  Bound: instruction issue.
+// One thread per track, walking every track of both sectors, made nearly
+// every one of a wave's iterations run the double part for a lane or two:
+// 787 us for 31k tracks and 3485 us for 126k, against 87 us and 468 us here.
+constexpr int kMatchWaves = 4;
+__global__ void __launch_bounds__(kMatchWaves * kWave) k_merge_match(DevPtrs d, MergeArgs m) {
+  const uint32_t nt = n_tracks(d), lane = threadIdx.x % kWave;
+  const uint32_t a = blockIdx.x * kMatchWaves + threadIdx.x / kWave;
   if (a >= nt) return;
   const MTrack ta = load_track(d, m, a);
   int32_t best = -1;
   double best_s = 0.0;
-  if (ta.phys >= 0) {
-    for (int side = 0; side < 2; ++side) {
-      const int32_t nb = m.nbr[2 * ta.sector + side];
-      if (nb < 0) continue;
-      const int step = side == 0 ? -1 : 1;
-      const double cd = m.cos20, sd = step * m.sin20;
-      const uint32_t b0 = m.sec_first[nb], b1 = m.sec_first[nb + 1];
-      for (uint32_t b = b0; b < b1; ++b) {
-        // rotation and propagation keep tan(lambda) and q/pT: their windows first
-        const float tlb = d.out_param[(size_t)b * 5 + 3], qb = d.out_param[(size_t)b * 5 + 4];
-        if (!(fabs(ta.p[3] - (double)tlb) <= m.dtanl && fabs(ta.p[4] - (double)qb) <= m.dqpt)) continue;
-        const MTrack tb = load_track(d, m, b);
-        if (!(tb.r_in > ta.r_in)) continue;
-        double x = ta.x, q[5];
+  const float tla = (float)ta.p[3], qa = (float)ta.p[4];
+  const float wt = (float)m.dtanl * 1.001f + 1e-6f, wq = (float)m.dqpt * 1.001f + 1e-5f;
+  for (int side = 0; ta.phys >= 0 && side < 2; ++side) {
+    const int32_t nb = m.nbr[2 * ta.sector + side];
+    if (nb < 0) continue;
+    // the rotation into the neighbour's frame is the same for every b
+    const int step = side == 0 ? -1 : 1;
+    double x = ta.x, q[5];
 #pragma unroll
-        for (int i = 0; i < 5; ++i) q[i] = ta.p[i];
-        if (!rotate_d(x, q, cd, sd, m.bk, nullptr)) continue;
-        if (!prop_d(q, x, tb.x, m.bk, m.s_max, nullptr)) continue;
-        const double dy = q[0] - tb.p[0], dz = q[1] - tb.p[1];
-        if (!(fabs(dy) <= m.dy && fabs(dz) <= m.dz && fabs(q[2] - tb.p[2]) <= m.dsinphi)) continue;
-        const double cyy = d.out_cov[(size_t)b * 15 + 0], czz = d.out_cov[(size_t)b * 15 + 2];
-        const double sc = dy * dy / (cyy + m.vy) + dz * dz / (czz + m.vz);
-        if (best < 0 || sc < best_s || (sc == best_s && (int32_t)b < best)) {
-          best = (int32_t)b;
-          best_s = sc;
-        }
-        const unsigned long long key = ((unsigned long long)__float_as_uint((float)sc) << 32) | a;
-        atomicMin(&m.pred_key[b], key);
+    for (int i = 0; i < 5; ++i) q[i] = ta.p[i];
+    if (!rotate_d(x, q, m.cos20, step * m.sin20, m.bk, nullptr)) continue;
+    if (!(fabs(q[2]) < m.s_max)) continue;   // no propagation starts there
+    // z within reach (lane 0: to the innermost row, lane 1: to the outermost)
+    const double end = d.rows[lane & 1u ? d.R - 1 : 0].x;
+    const double ze = q[1] + q[3] * path_bound(q[2], m.bk * q[4], end - x, m.s_max);
+    const double z0 = __shfl(ze, 0, kWave), z1 = __shfl(ze, 1, kWave);
+    const double slack = m.dz * 1.001 + 0.01 + 1e-4 * fabs(z1 - z0) + 1e-6 * fabs(q[1]);
+    const float zlo = (float)(fmin(z0, z1) - slack), zhi = (float)(fmax(z0, z1) + slack);
+    const uint32_t b0 = m.sec_first[nb], b1 = m.sec_first[nb + 1];
+    // first slot whose bin reaches the window, 64 probes at a time
+    const int klo = tan_bin(ta.p[3] - m.dtanl), khi = tan_bin(ta.p[3] + m.dtanl);
+    uint32_t lo = b0, hi = b1;
+    while (hi - lo > (uint32_t)kWave) {
+      const uint32_t st = (hi - lo + kWave - 1) / kWave, p = lo + lane * st;
+      const uint32_t below = (uint32_t)__popcll(__ballot(p < hi && tan_bin(m.sorted[p < hi ? p : lo].x) < klo));
+      hi = min(hi, lo + below * st);
+      if (below) lo += (below - 1) * st + 1;
+    }
+    {
+      const uint32_t p = lo + lane;
+      lo += (uint32_t)__popcll(__ballot(p < hi && tan_bin(m.sorted[p < hi ? p : b0].x) < klo));
+    }
+    for (uint32_t base = lo; base < b1; base += kWave) {
+      const bool in = base + lane < b1;
+      const float4 v = in ? m.sorted[base + lane] : make_float4(INFINITY, 0.0f, 0.0f, 0.0f);
+      if (tan_bin(__shfl(v.x, 0, kWave)) > khi) break;   // bins ascend
+      if (!(in && fabsf(tla - v.x) <= wt && fabsf(qa - v.y) <= wq && v.z >= zlo && v.z <= zhi)) continue;
+      const uint32_t b = __float_as_uint(v.w);
+      const MTrack tb = load_track(d, m, b);
+      if (!(fabs(ta.p[3] - tb.p[3]) <= m.dtanl && fabs(ta.p[4] - tb.p[4]) <= m.dqpt)) continue;
+      if (!(tb.r_in > ta.r_in)) continue;
+      double qb[5];
+#pragma unroll
+      for (int i = 0; i < 5; ++i) qb[i] = q[i];
+      if (!prop_d(qb, x, tb.x, m.bk, m.s_max, nullptr)) continue;
+      const double dy = qb[0] - tb.p[0], dz = qb[1] - tb.p[1];
+      if (!(fabs(dy) <= m.dy && fabs(dz) <= m.dz && fabs(qb[2] - tb.p[2]) <= m.dsinphi)) continue;
+      const double cyy = d.out_cov[(size_t)b * 15 + 0], czz = d.out_cov[(size_t)b * 15 + 2];
+      const double sc = dy * dy / (cyy + m.vy) + dz * dz / (czz + m.vz);
+      if (best < 0 || sc < best_s || (sc == best_s && (int32_t)b < best)) {
+        best = (int32_t)b;
+        best_s = sc;
+      }
+      const unsigned long long key = ((unsigned long long)__float_as_uint((float)sc) << 32) | a;
+      atomicMin(&m.pred_key[b], key);
+    }
+  }
+  if (__any(best >= 0)) {   // the lanes' best: smallest score, ties to the smaller index
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      const int32_t ob = __shfl_xor(best, off, kWave);
+      const double os = __shfl_xor(best_s, off, kWave);
+      if (ob >= 0 && (best < 0 || os < best_s || (os == best_s && ob < best))) {
+        best = ob;
+        best_s = os;
       }
     }
   }
-  m.succ[a] = best;
+  if (lane == 0) m.succ[a] = best;
 }
 
 __global__ void __launch_bounds__(kThreads) k_merge_link(DevPtrs d, MergeArgs m) {
@@ -281,109 +368,150 @@ __device__ __forceinline__ uint32_t row_of(const DevPtrs& d, uint32_t s, uint32_
   return lo;
 }
 
-__global__ void __launch_bounds__(kThreads) k_merge_emit(DevPtrs d, MergeArgs m, KfConst k) {
+// Per chain head: the chain's record, the cluster offset of each of its
+// segments, and its place in the list of chains to refit if it has several.
+__global__ void __launch_bounds__(kThreads) k_merge_heads(DevPtrs d, MergeArgs m) {
   const uint32_t nt = n_tracks(d);
   const uint32_t a = blockIdx.x * kThreads + threadIdx.x;
-  if (a >= nt || m.head_flag[a] == 0u) return;
-  const uint32_t c = m.head_scan[a];   // chain index
-  uint32_t o = m.cl_scan[a];
-  m.heads[c] = a;
-  m.first[c] = o;
-  int32_t last = (int32_t)a, nseg = 0;
-  for (int32_t t = (int32_t)a; t >= 0; t = m.next[t]) {
-    for (uint32_t j = d.out_first[t]; j < d.out_first[t + 1]; ++j) m.clusters[o++] = d.out_clusters[j];
-    m.head_of[t] = a;
-    last = t;
-    ++nseg;
+  const bool head = a < nt && m.head_flag[a] != 0u;
+  int32_t nseg = 0;
+  if (head) {
+    const uint32_t c = m.head_scan[a];   // chain index
+    uint32_t o = m.cl_scan[a];
+    m.heads[c] = a;
+    m.first[c] = o;
+    for (int32_t t = (int32_t)a; t >= 0; t = m.next[t]) {
+      m.seg_off[t] = o;
+      o += d.out_first[t + 1] - d.out_first[t];
+      m.head_of[t] = a;
+      ++nseg;
+    }
+    if (c + 1 == m.head_scan[nt]) m.first[c + 1] = o;
+    m.nseg[c] = nseg;
+    m.chi2[c] = d.out_chi2[a];
+    m.ndf[c] = 2 * (int32_t)(o - m.cl_scan[a]) - 5;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) m.param[(size_t)c * 5 + q] = d.out_param[(size_t)a * 5 + q];
+#pragma unroll
+    for (int q = 0; q < 15; ++q) m.cov[(size_t)c * 15 + q] = d.out_cov[(size_t)a * 15 + q];
   }
-  if (c + 1 == m.head_scan[nt]) m.first[c + 1] = o;
-  double P[5], C[15];
-  double chi2 = d.out_chi2[a];
-  const uint32_t ncl = o - m.first[c];
-  int32_t ndf = 2 * (int32_t)ncl - 5;
+  // one atomic per wave; the order of the refits does not matter
+  const unsigned long long multi = __ballot(nseg > 1);
+  const uint32_t lane = threadIdx.x % kWave;
+  uint32_t base = 0;
+  if (lane == 0 && multi) base = atomicAdd(&d.hdr->merge_refits, (uint32_t)__popcll(multi));
+  base = (uint32_t)__shfl((int)base, 0, kWave);
+  if (nseg > 1) m.refit[base + (uint32_t)__popcll(multi & ((1ull << lane) - 1ull))] = a;
+}
+
+// Per track, one wave: its clusters to their place in the chain's list and,
+// where the chain is refitted, each cluster's row.
+__global__ void __launch_bounds__(kThreads) k_merge_copy(DevPtrs d, MergeArgs m) {
+  const uint32_t nt = n_tracks(d), lane = threadIdx.x % kWave;
+  const uint32_t t = blockIdx.x * (kThreads / kWave) + threadIdx.x / kWave;
+  if (t >= nt) return;
+  const uint32_t j0 = d.out_first[t], n = d.out_first[t + 1] - j0, o = m.seg_off[t], s = d.out_sector[t];
+  const bool rows = m.next[t] >= 0 || m.has_pred[t] != 0u;
+  for (uint32_t j = lane; j < n; j += kWave) {
+    const uint32_t id = d.out_clusters[j0 + j];
+    m.clusters[o + j] = id;
+    if (rows) m.cl_row[o + j] = (uint8_t)row_of(d, s, id);
+  }
+}
+
+// Per chain of several segments, one lane: the inward pass over the chain's
+// clusters, from the outermost one of the last segment, in double.  Bound:
+// the latency of the dependent steps (few chains, no more than a wave or two
+// per SIMD), so the next clusters' ids and coordinates are loaded ahead and
+// their rows come from k_merge_copy (270 us for 31k tracks, 427 us for 126k,
+// and 22 and 73 us in k_merge_copy); with the rows searched and every load on
+// the chain, in the thread that also copied the clusters, it was 609 and
+// 829 us.
+__global__ void __launch_bounds__(kWave) k_merge_refit(DevPtrs d, MergeArgs m) {
+  const uint32_t k = blockIdx.x * kWave + threadIdx.x;
+  if (k >= d.hdr->merge_refits) return;
+  const uint32_t a = m.refit[k], c = m.head_scan[a];
+  const int32_t o0 = (int32_t)m.first[c];
+  int32_t seg = (int32_t)a;
+  while (m.next[seg] >= 0) seg = m.next[seg];
+  int32_t o = (int32_t)(m.seg_off[seg] + (d.out_first[seg + 1] - d.out_first[seg])) - 1;
+  uint32_t sec = d.out_sector[seg];
+  int32_t seg0 = (int32_t)m.seg_off[seg];   // first merged cluster of the current segment
+  // cluster o is in hand; o - 1's coordinates and o - 2's id are on their way
+  auto id_at = [&](int32_t q) { return m.clusters[q > o0 ? q : o0]; };
+  uint32_t row = m.cl_row[o], row1 = m.cl_row[o > o0 ? o - 1 : o0];
+  const uint32_t id0 = id_at(o), id1 = id_at(o - 1);
+  uint32_t id2 = id_at(o - 2);
+  const float y0 = d.y[id0], z0 = d.z[id0];
+  float y1 = d.y[id1], z1 = d.z[id1];
+  double p[5], cv[15];
+  double x = d.out_xref[seg];
 #pragma unroll
-  for (int q = 0; q < 5; ++q) P[q] = d.out_param[(size_t)a * 5 + q];
+  for (int q = 0; q < 5; ++q) p[q] = d.out_param[(size_t)seg * 5 + q];
+  double ch = 0.0;
+  bool ok = prop_d(p, x, d.rows[row].x, m.bk, m.s_max, nullptr);
+  if (ok) {
+    x = d.rows[row].x;
+    p[0] = y0;
+    p[1] = z0;
 #pragma unroll
-  for (int q = 0; q < 15; ++q) C[q] = d.out_cov[(size_t)a * 15 + q];
-  if (nseg > 1) {
-    // inward pass over the chain's clusters, from the outermost one of the last segment
-    const double vy = m.vy, vz = m.vz;
-    int32_t seg = last;
-    uint32_t j = d.out_first[seg + 1] - 1;
-    uint32_t sec = d.out_sector[seg];
-    uint32_t id = d.out_clusters[j];
-    uint32_t row = row_of(d, sec, id);
-    double p[5], cv[15];
-    double x = d.out_xref[seg];
-#pragma unroll
-    for (int q = 0; q < 5; ++q) p[q] = d.out_param[(size_t)seg * 5 + q];
-    bool ok = prop_d(p, x, d.rows[row].x, m.bk, m.s_max, nullptr);
-    double ch = 0.0;
-    if (ok) {
-      x = d.rows[row].x;
-      p[0] = d.y[id];
-      p[1] = d.z[id];
-#pragma unroll
-      for (int q = 0; q < 15; ++q) cv[q] = 0.0;
-      cv[0] = vy;
-      cv[2] = vz;
-      cv[5] = m.c0_sinphi;
-      cv[9] = m.c0_tanl;
-      cv[14] = m.c0_qpt;
-      // walk back: earlier clusters of this segment, then the previous segments
-      for (;;) {
-        if (j > d.out_first[seg]) {
-          --j;
-        } else {
-          // previous segment in the chain: the one whose next is seg
-          int32_t pv = (int32_t)a;
-          while (m.next[pv] != seg) pv = m.next[pv];
-          const int step = (m.phys[d.out_sector[pv]] % kSide - m.phys[sec] % kSide + kSide) % kSide == 1 ? 1 : -1;
-          if (!rotate_d(x, p, m.cos20, step * m.sin20, m.bk, cv)) { ok = false; break; }
-          seg = pv;
-          sec = d.out_sector[seg];
-          j = d.out_first[seg + 1] - 1;
-        }
-        id = d.out_clusters[j];
-        row = row_of(d, sec, id);
-        if (!prop_d(p, x, d.rows[row].x, m.bk, m.s_max, cv)) { ok = false; break; }
-        x = d.rows[row].x;
-        update_d(p, cv, d.y[id], d.z[id], vy, vz, ch);
-        if (seg == (int32_t)a && j == d.out_first[a]) break;
+    for (int q = 0; q < 15; ++q) cv[q] = 0.0;
+    cv[0] = m.vy;
+    cv[2] = m.vz;
+    cv[5] = m.c0_sinphi;
+    cv[9] = m.c0_tanl;
+    cv[14] = m.c0_qpt;
+    while (o > o0) {
+      if (o == seg0) {
+        // previous segment in the chain: the one whose next is seg
+        int32_t pv = (int32_t)a;
+        while (m.next[pv] != seg) pv = m.next[pv];
+        const int step = (m.phys[d.out_sector[pv]] % kSide - m.phys[sec] % kSide + kSide) % kSide == 1 ? 1 : -1;
+        if (!rotate_d(x, p, m.cos20, step * m.sin20, m.bk, cv)) { ok = false; break; }
+        seg = pv;
+        sec = d.out_sector[seg];
+        seg0 = (int32_t)m.seg_off[seg];
       }
-    }
-    if (ok) {
-#pragma unroll
-      for (int q = 0; q < 5; ++q) P[q] = p[q];
-#pragma unroll
-      for (int q = 0; q < 15; ++q) C[q] = cv[q];
-      chi2 = ch;
-    } else {
-      ndf = -1;
+      --o;
+      row = row1;
+      const float ym = y1, zm = z1;
+      y1 = d.y[id2];
+      z1 = d.z[id2];
+      id2 = id_at(o - 2);
+      row1 = m.cl_row[o > o0 ? o - 1 : o0];
+      const double xr = d.rows[row].x;
+      if (!prop_d(p, x, xr, m.bk, m.s_max, cv)) { ok = false; break; }
+      x = xr;
+      update_d(p, cv, ym, zm, m.vy, m.vz, ch);
     }
   }
+  if (!ok) {
+    m.ndf[c] = -1;   // the chain keeps its first segment's result
+    return;
+  }
 #pragma unroll
-  for (int q = 0; q < 5; ++q) m.param[(size_t)c * 5 + q] = (float)P[q];
+  for (int q = 0; q < 5; ++q) m.param[(size_t)c * 5 + q] = (float)p[q];
 #pragma unroll
-  for (int q = 0; q < 15; ++q) m.cov[(size_t)c * 15 + q] = (float)C[q];
-  m.chi2[c] = (float)chi2;
-  m.ndf[c] = ndf;
-  m.nseg[c] = nseg;
+  for (int q = 0; q < 15; ++q) m.cov[(size_t)c * 15 + q] = (float)cv[q];
+  m.chi2[c] = (float)ch;
 }
 
 }  // namespace
 
-void launch_merge(const DevPtrs& d, const MergeArgs& m, const KfConst& k, uint32_t nt, hipStream_t s) {
+void launch_merge(const DevPtrs& d, const MergeArgs& m, uint32_t nt, hipStream_t s) {
+  hipLaunchKernelGGL(k_merge_prep, dim3(d.S), dim3(kPrepThreads), 0, s, d, m);
+  if (nt == 0) return;
   const uint32_t g = (nt + kThreads - 1) / kThreads;
-  hipLaunchKernelGGL(k_merge_ranges, dim3((d.S + 1 + kThreads - 1) / kThreads), dim3(kThreads), 0, s, d, m);
-  if (g == 0) return;
-  hipLaunchKernelGGL(k_merge_init, dim3(g), dim3(kThreads), 0, s, d, m, nt);
-  hipLaunchKernelGGL(k_merge_match, dim3(g), dim3(kThreads), 0, s, d, m, k);
+  const uint32_t waves = kThreads / kWave;
+  hipLaunchKernelGGL(k_merge_match, dim3((nt + kMatchWaves - 1) / kMatchWaves), dim3(kMatchWaves * kWave), 0, s, d, m);
   hipLaunchKernelGGL(k_merge_link, dim3(g), dim3(kThreads), 0, s, d, m);
   hipLaunchKernelGGL(k_merge_count, dim3(g), dim3(kThreads), 0, s, d, m);
   launch_scan_u32(m.head_flag, m.head_scan, nt, d.scan_blocks, s);
   launch_scan_u32(m.chain_clusters, m.cl_scan, nt, d.scan_blocks, s);
-  hipLaunchKernelGGL(k_merge_emit, dim3(g), dim3(kThreads), 0, s, d, m, k);
+  hipLaunchKernelGGL(k_merge_heads, dim3(g), dim3(kThreads), 0, s, d, m);
+  hipLaunchKernelGGL(k_merge_copy, dim3((nt + waves - 1) / waves), dim3(kThreads), 0, s, d, m);
+  // a chain to refit has at least two tracks
+  hipLaunchKernelGGL(k_merge_refit, dim3((nt / 2 + kWave - 1) / kWave + 1), dim3(kWave), 0, s, d, m);
 }
 
 }  // namespace tpc

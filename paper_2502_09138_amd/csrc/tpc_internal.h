@@ -49,7 +49,7 @@ struct ResultHeader {
   uint32_t n_starts;       // C4 count (may exceed capacity; see flags)
   uint32_t error_flags;
   uint32_t n_tracks;
-  uint32_t pad0;
+  uint32_t merge_refits;   // chains of several segments in the last C8 (the refits of C9)
   uint64_t n_track_clusters;
   uint64_t n_steps;        // row steps taken by all tracklet lanes (C5 work measure)
   uint32_t codec_escaped;  // clusters the last C10 encoding stored raw
@@ -152,6 +152,11 @@ struct MergeArgs {
   float* chi2;                         // [MT]
   int32_t* ndf;                        // [MT] -1: refit failed
   int32_t* nseg;                       // [MT]
+  // scratch of the completed request
+  float4* sorted;                      // [n_tracks] tracks by (sector, tan(lambda) bin): (tan(lambda), q/pT, z, track)
+  uint32_t* seg_off;                   // [n_tracks] first merged cluster of each track
+  uint32_t* refit;                     // [n_tracks] heads of the chains to refit
+  uint8_t* cl_row;                     // [n_track_clusters] row of each merged cluster (refitted chains only)
   double cos20, sin20;                 // the rotation between neighbouring sectors
   double bk, s_max;                    // -c_B * Bz and the |sin phi| limit, in double
   double vy, vz, c0_sinphi, c0_tanl, c0_qpt;   // measurement and initial variances, in double
@@ -218,7 +223,7 @@ void launch_links(const DevPtrs& d, uint32_t max_row_hits, hipStream_t s);
 void launch_clean_starts(const DevPtrs& d, uint32_t max_row_hits, hipStream_t s);
 void launch_tracklets(const DevPtrs& d, const KfConst& k, uint32_t max_row_hits, hipStream_t s);
 void launch_select(const DevPtrs& d, const KfConst& k, uint32_t tile_rows, hipStream_t s);
-void launch_merge(const DevPtrs& d, const MergeArgs& m, const KfConst& k, uint32_t n_tracks, hipStream_t s);
+void launch_merge(const DevPtrs& d, const MergeArgs& m, uint32_t n_tracks, hipStream_t s);
 void launch_codec_encode(const CodecArgs& a, unsigned long long* scan_blocks, hipStream_t s);
 void launch_codec_decode(const DecodeArgs& a, hipStream_t s);
 // exclusive scans; n read from *n_dev when n_dev != nullptr (then n_max bounds the grid)

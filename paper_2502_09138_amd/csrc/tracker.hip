@@ -567,7 +567,7 @@ __global__ void k_begin(ResultHeader* h) {
   h->n_starts = 0;
   h->error_flags = 0;
   h->n_tracks = 0;
-  h->pad0 = 0;
+  h->merge_refits = 0;
   h->codec_escaped = 0;
   h->codec_unassigned = 0;
   h->n_track_clusters = 0;
@@ -888,6 +888,13 @@ tpc_status tpc_merge_sectors(tpc_tracker* t, uint64_t request_id, const int32_t*
   m.chi2 = (float*)(w + L.m_chi2);
   m.ndf = (int32_t*)(w + L.m_ndf);
   m.nseg = (int32_t*)(w + L.m_nseg);
+  // scratch of the completed request: the K5 refit records (100 B per tracklet) hold the sorted tracks (16 B
+  // per track), the successor and predecessor words are free once the links are made, the C6 per-tile counts
+  // (R bytes per tracklet) hold a byte per track cluster (at most R per track)
+  m.sorted = (float4*)t->d.k5_rec;
+  m.seg_off = (uint32_t*)m.pred_key;
+  m.refit = (uint32_t*)m.succ;
+  m.cl_row = t->d.own_part;
   m.cos20 = std::cos(20.0 * 3.14159265358979323846 / 180.0);
   m.sin20 = std::sin(20.0 * 3.14159265358979323846 / 180.0);
   const tpc_tracker_config& c = t->cfg;
@@ -907,7 +914,7 @@ tpc_status tpc_merge_sectors(tpc_tracker* t, uint64_t request_id, const int32_t*
   hipStream_t st = t->stream;
   HIP_TRY(hipMemcpyAsync((void*)m.phys, t->h_phys, (size_t)S * 4, hipMemcpyHostToDevice, st));
   const uint32_t n = h.n_tracks;
-  launch_merge(t->d, m, t->kc, n, st);
+  launch_merge(t->d, m, n, st);
   HIP_TRY(hipGetLastError());
   // counts, then the arrays
   uint32_t* cnt = (uint32_t*)(t->h_merge + (HL.m_head_scan - HL.m_next));

@@ -123,3 +123,28 @@ def test_merge_without_neighbours_changes_nothing(torch_cuda):
     assert np.all(mg["next"] == -1) and len(mg["heads"]) == tracks.n_tracks
     assert np.array_equal(mg["param"], tracks.param) and np.array_equal(mg["clusters"], tracks.cluster_ids)
     tr.close()
+
+
+@pytest.mark.parametrize("n_tracks, windows", [(1, {}), (30, {}), (700, {}),
+                                               (60, dict(merge_dtanl=10.0, merge_dqpt=100.0, merge_dz=1e4)),
+                                               (300, dict(merge_dtanl=1e-4, merge_dz=0.3))])
+def test_merge_candidates_over_sizes_and_windows(torch_cuda, n_tracks, windows):
+    """The candidate lists (tan(lambda) bins, reachable z) against the oracle's walk over every pair: sectors of a
+    few tracks, more than one wave of slots, windows wider than the bins and narrower than one.  A link may
+    differ where a track or a score differs within rounding, so at most 0.5% (the file's bar), and at most one
+    where there are fewer than 200 links."""
+    from paper_2502_09138_amd.tracker import Tracker
+    ev = synth.boundary_crossers(seed=11, n_tracks=n_tracks)
+    print("case: boundary_crossers n_tracks", n_tracks, windows, "N=", ev.n_clusters, flush=True)
+    cfg = default_config(**windows)
+    tr = Tracker(cfg, max_clusters=max(64, ev.n_clusters), max_sectors=ev.n_sectors)
+    tracks, mg = tr.track_and_merge(ev.y, ev.z, ev.row_offsets, ev.sector_z_lo, ev.sector_z_hi, [0, 1, 2], host=True)
+    tr.close()
+    run = oracle.Run.from_event(cfg.as_dict(), ev).run_all()
+    res, mo = run.result(), oracle.merge(run, [0, 1, 2])
+    st_o = res["starts"][res["trk_tracklet"]].astype(np.int64)
+    start = tracks.start.astype(np.int64)
+    o_links = {(int(st_o[a]), int(st_o[b])) for a, b in enumerate(mo["next"]) if b >= 0}
+    g_links = {(int(start[a]), int(start[b])) for a, b in enumerate(mg["next"]) if b >= 0}
+    print("links", len(o_links), len(g_links), "common", len(o_links & g_links), flush=True)
+    assert len(o_links ^ g_links) <= max(1, 0.005 * len(o_links))
