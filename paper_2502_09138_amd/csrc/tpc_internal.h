@@ -53,7 +53,7 @@ struct ResultHeader {
   uint64_t n_track_clusters;
   uint64_t n_steps;        // row steps taken by all tracklet lanes (C5 work measure)
   uint32_t codec_escaped;  // clusters the last C10 encoding stored raw
-  uint32_t codec_unassigned;  // clusters on no track in the last C10 encoding (host copy of the scan total)
+  uint32_t codec_unassigned;  // clusters on no track in the last C10 encoding
 };
 
 // All device pointers of one request.
@@ -188,11 +188,17 @@ struct CodecArgs {
   float* raw;                  // [2 * n_cl]
   uint8_t* un_row;             // [N]
   float* un_yz;                // [2 * N]
+  // ownership of the completed request (C6)
+  const uint32_t* sector;      // [n_tracks]
+  const uint32_t* W;           // [N] ownership word per sorted position
+  const uint32_t* sid;         // [N] input cluster per sorted position
+  const unsigned long long* tk_pack;   // [tracklets] bit 0: accepted
   // workspace scratch
-  uint32_t* unf;               // [N] 1 = on no track
+  uint32_t* un_bits;           // [N] per row, from its first word: bit i = input cluster i of the row is on no track
   uint32_t* row_cnt;           // [SR] clusters on no track per (sector, row)
   uint32_t* row_pos;           // [SR + 1] exclusive scan of row_cnt
   uint32_t* n_escaped;
+  uint32_t* n_unassigned;
 };
 
 // C11 decoding of a stream into cluster arrays.
@@ -208,6 +214,7 @@ struct DecodeArgs {
   uint32_t n_tracks;
   uint64_t n_cl, n_un;
   const RowConst* rows;
+  uint32_t R;
   float q_y, q_z;
   float* y_out;                // [n_cl + n_un]
   float* z_out;

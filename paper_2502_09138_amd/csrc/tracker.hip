@@ -11,6 +11,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -999,18 +1000,22 @@ tpc_status tpc_encode_tracks(tpc_tracker* t, uint64_t request_id, float q_y, flo
   a.raw = out->raw;
   a.un_row = out->un_row;
   a.un_yz = out->un_yz;
-  // scratch of the completed request: the C6 ownership words (one per
-  // cluster) and the C4 / K5 per-row counts
-  a.unf = d.W;
+  a.sector = d.out_sector;
+  a.W = d.W;
+  a.sid = d.sid;
+  a.tk_pack = d.tk_pack;
+  // scratch of the completed request: the C2 up links (one word per cluster)
+  // and the C4 / K5 per-row counts
+  a.un_bits = (uint32_t*)d.up0;
   a.row_cnt = d.row_nstart;
   a.row_pos = d.k5_off;
   a.n_escaped = &d.hdr->codec_escaped;
+  a.n_unassigned = &d.hdr->codec_unassigned;
   hipStream_t st = t->stream;
   launch_codec_encode(a, d.scan_blocks, st);
   HIP_TRY(hipGetLastError());
-  uint32_t* cnt = reinterpret_cast<uint32_t*>(&t->h_hdr->codec_escaped);
-  HIP_TRY(hipMemcpyAsync(cnt, a.n_escaped, 4, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(&t->h_hdr->codec_unassigned, a.row_pos + a.SR, 4, hipMemcpyDeviceToHost, st));
+  static_assert(offsetof(ResultHeader, codec_unassigned) == offsetof(ResultHeader, codec_escaped) + 4, "one copy");
+  HIP_TRY(hipMemcpyAsync(&t->h_hdr->codec_escaped, a.n_escaped, 8, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   counts->n_tracks = a.n_tracks;
   counts->n_track_clusters = a.n_cl;
@@ -1042,6 +1047,7 @@ tpc_status tpc_decode_tracks(tpc_tracker* t, const tpc_codec_stream* in, const t
   a.n_cl = counts->n_track_clusters;
   a.n_un = counts->n_unassigned;
   a.rows = t->d.rows;
+  a.R = (uint32_t)t->cfg.n_rows;
   a.q_y = q_y;
   a.q_z = q_z;
   a.y_out = y_out;

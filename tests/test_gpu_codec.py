@@ -124,3 +124,38 @@ def test_codec_rejects_bad_arguments(torch_cuda):
     finally:
         tr.release(rid)
         tr.close()
+
+
+@pytest.mark.parametrize("lengths, shift", [([1], 0), ([2047], 0), ([2048], 1), ([2049], 0), ([70] * 100, 0), ([70] * 100, 1),
+                                            ([3, 0, 0, 9] * 300, 0), ([1] * 3000, 0), ([7] * 900, 1), ([0] * 600 + [4100], 0)])
+def test_decode_windows_and_alignment(torch_cuda, lengths, shift):
+    """Streams of any track lengths against the oracle, bit for bit: workgroups whose clusters are of one track, of
+    more tracks than are staged, of empty ones; ends inside a group of four; arrays that start off a 16-byte unit."""
+    from paper_2502_09138_amd.tracker import Tracker
+    torch = torch_cuda
+    rng = np.random.default_rng(len(lengths) + shift)
+    cfg = default_config()
+    n, nc, nu = len(lengths), int(np.sum(lengths)), 37
+    st = dict(coef=rng.normal(0, 1, (n, 6)).astype(np.float32), x_ref=rng.uniform(85, 233, n).astype(np.float32),
+              first=np.concatenate([[0], np.cumsum(lengths)]).astype(np.uint32),
+              row=rng.integers(0, synth.N_ROWS, nc).astype(np.uint8), code=rng.integers(-99, 99, (nc, 2)).astype(np.int16),
+              raw=rng.normal(0, 9, (nc, 2)).astype(np.float32), un_row=rng.integers(0, synth.N_ROWS, nu).astype(np.uint8),
+              un_yz=rng.normal(0, 9, (nu, 2)).astype(np.float32))
+    st["code"][rng.random(nc) < 0.02] = (-32768, 0)
+    print("case: decode", n, "tracks", nc, "clusters, shift", shift, flush=True)
+
+    def on_gpu(a):
+        a = a.view(np.int32) if a.dtype == np.uint32 else a
+        b = torch.zeros((len(a) + 1,) + a.shape[1:], dtype=torch.from_numpy(a[:0]).dtype, device="cuda")
+        b[shift:shift + len(a)] = torch.from_numpy(a)
+        return b[shift:shift + len(a)]
+
+    tr = Tracker(cfg, max_clusters=64, max_sectors=1)
+    y, z, row = (v.cpu().numpy() for v in tr.decode({k: on_gpu(v) for k, v in st.items()},
+                                                    dict(n_tracks=n, n_track_clusters=nc, n_unassigned=nu, n_escaped=0),
+                                                    0.01, 0.015))
+    tr.close()
+    oy, oz = oracle.codec_decode(cfg.row_x, 0.01, 0.015, st)
+    for got, ref in ((y, np.concatenate([oy[:nc], st["un_yz"][:, 0]])), (z, np.concatenate([oz[:nc], st["un_yz"][:, 1]]))):
+        assert np.array_equal(got.view(np.int32), ref.astype(np.float32).view(np.int32))
+    assert np.array_equal(row, np.concatenate([st["row"], st["un_row"]]))
