@@ -32,11 +32,9 @@ __device__ __forceinline__ int bin1(float v, float lo, float inv_w, int n) {
 #pragma clang fp contract(off)
   const float a = v - lo;
   const float b = (float)n * inv_w;
-  float u = a * b;
-  if (!(u >= 0.0f)) u = 0.0f;
-  const float top = (float)(n - 1);
-  if (u > top) u = top;
-  return (int)u;
+  const float u = a * b;
+  // clamp to [0, n - 1]; NaN (where the definition says 0) takes the minimum of the other two
+  return (int)__builtin_amdgcn_fmed3f(u, 0.0f, (float)(n - 1));
 }
 
 __device__ __forceinline__ uint32_t bin_base(const DevPtrs& d, uint32_t sr) { return d.row_off[sr] + 2u * sr; }

@@ -34,7 +34,7 @@ struct SectorConst {
 struct KfConst {
   float bk;            // -c_B * Bz
   float s_max, qpt_max;
-  float vy, vz;        // sigma^2
+  double vyd, vzd;     // the float32 sigma^2 as doubles (no conversion per step)
   float c0_sinphi, c0_tanl, c0_qpt;
   float gate, cap, margin;
   float rho;

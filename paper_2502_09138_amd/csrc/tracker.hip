@@ -443,8 +443,8 @@ tpc_status tpc_tracker_create(const tpc_tracker_config* cfg, tpc_tracker** out) 
   k.bk = (float)(-kCB * cfg->bz_tesla);
   k.s_max = (float)cfg->s_max;
   k.qpt_max = (float)cfg->seed_qpt_max;
-  k.vy = (float)(cfg->sigma_y * cfg->sigma_y);
-  k.vz = (float)(cfg->sigma_z * cfg->sigma_z);
+  k.vyd = (float)(cfg->sigma_y * cfg->sigma_y);
+  k.vzd = (float)(cfg->sigma_z * cfg->sigma_z);
   k.c0_sinphi = (float)cfg->c0_sinphi;
   k.c0_tanl = (float)cfg->c0_tanl;
   k.c0_qpt = (float)cfg->c0_qpt;

@@ -192,7 +192,7 @@ __device__ __forceinline__ void update(Trk& t, float ym, float zm, const KfConst
   using P = par_t;
   using V = cov_t;
   V* c = t.c;
-  const V vy = k.vy, vz = k.vz;
+  const V vy = k.vyd, vz = k.vzd;
   const V r0 = V(P(ym) - t.p[0]), r1 = V(P(zm) - t.p[1]);
   const V S00 = c[0] + vy, S01 = c[1], S11 = c[2] + vz;
   const V id = frcp(S00 * S11 - S01 * S01);
@@ -220,23 +220,30 @@ __device__ __forceinline__ void update(Trk& t, float ym, float zm, const KfConst
 __device__ __forceinline__ void set_c0(Trk& t, const KfConst& k) {
 #pragma unroll
   for (int i = 0; i < 15; ++i) t.c[i] = cov_t(0);
-  t.c[tri(0, 0)] = k.vy;
-  t.c[tri(1, 1)] = k.vz;
+  t.c[tri(0, 0)] = k.vyd;
+  t.c[tri(1, 1)] = k.vzd;
   t.c[tri(2, 2)] = k.c0_sinphi;
   t.c[tri(3, 3)] = k.c0_tanl;
   t.c[tri(4, 4)] = k.c0_qpt;
 }
 
 // Grid search in row sr for the candidate closest to the prediction; -1 if
-// none, else its position, with its (y, z) in hv.  z-lines are walked as one
-// flat sequence of candidate groups per lane (see search_lds); the kGroup loads
-// of a group are issued together.
+// none, else its position, with its (y, z) in hv.  The hits of the bins that
+// the window touches are tested in ascending position, kGroup of them at a
+// time (their loads are contiguous and issued together).  Where a z-line has
+// few bins, its bins and those of the next lines are taken as one run: the
+// hits between them are outside the window and fail its test, and a lane
+// whose window straddles two lines does not cost its wave a second group.
 constexpr int kGroup = 6;   // measured on the 32-orbit frame: 4 -> 6 is -3.7% in K5, 8 and above slower
 constexpr int kGroupLds = 4;   // candidates per group of the LDS search
+constexpr int kRunBins = 3;    // z-lines of at most this many bins are searched as one run
+
+// two consecutive hits with one 16-byte load (hits are 8-byte aligned)
+typedef f32x4 f32x4_at8 __attribute__((aligned(8)));
 
 __device__ __forceinline__ int32_t search_m(const DevPtrs& d, uint2 meta, const RowK& rk, const SectorConst& sc,
                                             const Trk& t, const KfConst& k, float zref, float2& hv) {
-  const float sy2 = float(t.c[0] + cov_t(k.vy)), sz2 = float(t.c[2] + cov_t(k.vz));
+  const float sy2 = float(t.c[0] + k.vyd), sz2 = float(t.c[2] + k.vzd);
   const float wy = fminf(k.gate * fsqrt(sy2), k.cap), wz = fminf(k.gate * fsqrt(sz2), k.cap);
   const float isy = frcp(sy2), isz = frcp(sz2);
   const float yp = float(t.p[0]), zp = float(t.p[1]);          // zp relative to zref
@@ -246,32 +253,41 @@ __device__ __forceinline__ int32_t search_m(const DevPtrs& d, uint2 meta, const 
   const int iy1 = bin1((yp + wy) + kWinPad, rk.y_lo, rk.inv_wy, ny);
   const int iz0 = bin1((za - wz) - kWinPad, sc.z_lo, sc.inv_wz, nz);
   const int iz1 = bin1((za + wz) + kWinPad, sc.z_lo, sc.inv_wz, nz);
-  const uint32_t* bs = d.bin_start + meta.x;
+  // bins [b0, b1] of the first run, which ends in the z-line of bin b1; e: the last bin of the window
+  uint32_t b0 = meta.x + (uint32_t)(iz0 * ny + iy0);
+  const uint32_t e = meta.x + (uint32_t)(iz1 * ny + iy1);
+  uint32_t b1 = ny <= kRunBins ? e : b0 + (uint32_t)(iy1 - iy0);
+  uint32_t q = d.bin_start[b0], hi = d.bin_start[b1 + 1];
   int32_t best = -1;
-  float bd = 0.0f;
-  int iz = iz0;
-  uint32_t q = bs[iz * ny + iy0], hi = bs[iz * ny + iy1 + 1];
+  float bd = INFINITY;
   for (;;) {
-    while (q >= hi && iz < iz1) {
-      ++iz;
-      q = bs[iz * ny + iy0];
-      hi = bs[iz * ny + iy1 + 1];
+    while (q >= hi && b1 < e) {
+      b0 += (uint32_t)ny;
+      b1 += (uint32_t)ny;
+      q = d.bin_start[b0];
+      hi = d.bin_start[b1 + 1];
     }
     if (q >= hi) break;
+    // up to kGroup - 1 entries past the run's end are read (the array is followed by others in the workspace)
+    // and not used
     float2 h[kGroup];
+    const f32x4_at8* src = reinterpret_cast<const f32x4_at8*>(d.syz + q);
 #pragma unroll
-    for (int j = 0; j < kGroup; ++j) h[j] = d.syz[min(q + j, hi - 1)];
+    for (int j = 0; j < kGroup / 2; ++j) {
+      const f32x4 v = src[j];
+      h[2 * j] = make_float2(v.x, v.y);
+      h[2 * j + 1] = make_float2(v.z, v.w);
+    }
+    const uint32_t n = hi - q;
 #pragma unroll
     for (int j = 0; j < kGroup; ++j) {
       const float dy = h[j].x - yp, dz = (h[j].y - zref) - zp;
-      if (q + j < hi && fabsf(dy) <= wy && fabsf(dz) <= wz) {
-        const float dd = dy * dy * isy + dz * dz * isz;
-        if (best < 0 || dd < bd) {
-          best = (int32_t)(q + j);
-          bd = dd;
-          hv = h[j];
-        }
-      }
+      const float dd = __builtin_fmaf(dy * dy, isy, (dz * dz) * isz);
+      const bool take = (uint32_t)j < n & fabsf(dy) <= wy & fabsf(dz) <= wz & dd < bd;
+      best = take ? (int32_t)(q + j) : best;
+      bd = take ? dd : bd;
+      hv.x = take ? h[j].x : hv.x;
+      hv.y = take ? h[j].y : hv.y;
     }
     q += kGroup;
   }
@@ -298,7 +314,7 @@ __device__ __forceinline__ int pair_swap(int v) {   // value of the other lane o
 __device__ __forceinline__ int32_t search_lds(const float2* yz, const uint32_t* bs, uint32_t first, uint2 meta,
                                               const RowK& rk, const SectorConst& sc, const Trk& t, const KfConst& k,
                                               float zref, uint32_t half) {
-  const float sy2 = float(t.c[0] + cov_t(k.vy)), sz2 = float(t.c[2] + cov_t(k.vz));
+  const float sy2 = float(t.c[0] + k.vyd), sz2 = float(t.c[2] + k.vzd);
   const float wy = fminf(k.gate * fsqrt(sy2), k.cap), wz = fminf(k.gate * fsqrt(sz2), k.cap);
   const float isy = frcp(sy2), isz = frcp(sz2);
   const float yp = float(t.p[0]), zp = float(t.p[1]);
