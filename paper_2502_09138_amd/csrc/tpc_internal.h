@@ -93,6 +93,7 @@ struct DevPtrs {
   uint32_t* k5_off;          // [SR+1] lane-per-tracklet K5: refit bucket offsets (sector, outermost row)
   uint32_t* k5_perm;         // [Tcap] tracklets in bucket order
   uint32_t* k5_inv;          // [Tcap] bucket slot of each tracklet
+  uint32_t* k5_order;        // [Tcap / 64 + 1] waves in starting order (the space of tk_pack, which C6 writes later)
   uint32_t* k5_rec;          // [25 * Tcap] refit results in slot order (one record per tracklet)
   // C6
   uint32_t* W;               // [N] ownership word (32-bit key) per sorted position

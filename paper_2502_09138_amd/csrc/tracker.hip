@@ -299,6 +299,7 @@ void carve(tpc_tracker* t) {
   d.W = (uint32_t*)(w + lay.W);
   d.own_part = (uint8_t*)(w + lay.own_part);
   d.tk_pack = (unsigned long long*)(w + lay.tk_pack);
+  d.k5_order = (uint32_t*)d.tk_pack;
   d.tk_scan = (unsigned long long*)(w + lay.tk_scan);
   d.acc_list = (uint32_t*)(w + lay.acc_list);
   d.out_sector = (uint32_t*)(w + lay.out_sector);
