@@ -438,9 +438,10 @@ tpc_status tpc_set_tracklet_schedule(tpc_tracker* t, int32_t schedule);
  *   TPC_KNOB_REFIT_ORDER        0 the lane-per-tracklet pipeline refits in
  *                               (sector, outermost row) order, 1 in tracklet
  *                               order
- *   TPC_KNOB_LINK_SLOTS         0 auto (8), 4 or 8: C2 up-row candidates held
- *                               per hit before the pair search falls back to
- *                               rescanning the window
+ *   TPC_KNOB_LINK_SLOTS         0 auto (8), 4 or 8: how much of the adjacent
+ *                               rows a C2 wave stages and how long its
+ *                               candidate lists are (4 for sparse rows, 8 for
+ *                               dense ones)
  *   TPC_KNOB_LINK_GROUP         0 auto (64), 1..4096: consecutive C2 tiles
  *                               (64 hits each) given to one XCD before the
  *                               next XCD's group (1 deals them out one by

@@ -52,6 +52,8 @@ struct ResultHeader {
   uint32_t merge_refits;   // chains of several segments in the last C8 (the refits of C9)
   uint64_t n_track_clusters;
   uint64_t n_steps;        // row steps taken by all tracklet lanes (C5 work measure)
+  uint32_t link_retries;   // K2 tiles left to the large stage
+  uint32_t pad0;
   uint32_t codec_escaped;  // clusters the last C10 encoding stored raw
   uint32_t codec_unassigned;  // clusters on no track in the last C10 encoding
 };
@@ -84,6 +86,7 @@ struct DevPtrs {
   uint32_t* wave_off;        // [S+1] row-synchronous K5: first wave of each sector
   const uint32_t* tile_off;  // [SR+1] K2: first tile of each row (ceil(N_r / kLinkTile) tiles per row)
   uint32_t* tile_sr;         // [tiles] K2: row of each tile (written by K1)
+  uint32_t* link_retry;      // [tiles <= N] K2 tiles left to the large stage (the space of up1, which C3 writes later)
   // C5
   int32_t* tk_rowhit;        // [R * Tcap]
   int32_t* tk_info;          // [4 * Tcap]: nHits, r_in, r_out, r0
@@ -119,7 +122,7 @@ struct DevPtrs {
   float rho;                 // (sigma_y / sigma_z)^2, float32
   int32_t k5_mode;           // 0 auto, 1 lane-per-tracklet pipeline, 2 row-synchronous
   int32_t k5_refit_order;    // 0 (sector, outermost row) buckets, 1 tracklet order
-  int32_t k2_slots;          // K2 up-candidate slots per lane: 4 or 8 (0 = 8)
+  int32_t k2_slots;          // K2 stage and lists: 4 for sparse rows, 8 for dense ones (0 = 8)
   uint32_t k2_group;         // K2 tiles per XCD group (1: round robin, kLinkGroupEighth: an eighth of the tiles)
   uint32_t k6_threads;       // workgroup size of the K6 tile kernels: 256, 512 or 1024
   uint32_t S, R, SR, N;

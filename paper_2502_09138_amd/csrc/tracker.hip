@@ -279,6 +279,7 @@ void carve(tpc_tracker* t) {
   d.down0 = (int32_t*)(w + lay.down0);
   d.up1 = (int32_t*)(w + lay.up1);
   d.down1 = (int32_t*)(w + lay.down1);
+  d.link_retry = (uint32_t*)d.up1;
   d.sflag = (uint8_t*)(w + lay.sflag);
   d.row_nstart = (uint32_t*)(w + lay.row_nstart);
   d.row_start_off = (uint32_t*)(w + lay.row_start_off);
@@ -570,6 +571,8 @@ __global__ void k_begin(ResultHeader* h) {
   h->error_flags = 0;
   h->n_tracks = 0;
   h->merge_refits = 0;
+  h->link_retries = 0;
+  h->pad0 = 0;
   h->codec_escaped = 0;
   h->codec_unassigned = 0;
   h->n_track_clusters = 0;
