@@ -128,6 +128,8 @@ struct DevPtrs {
   uint32_t S, R, SR, N;
   uint32_t tcap;
   uint32_t tile_cap;         // LDS words of one selector tile (max hits in a sector's row block)
+  uint32_t max_sector_hits;  // hits of the largest sector
+  uint32_t res_blocks;       // K5: workgroups of 128 tracklets over all sectors, at a tracklet per 16 hits
   uint32_t n_link_tiles;     // K2 tiles of this request
   uint32_t n_packs;          // K1 row packs of this request
   uint32_t max_tracks;
@@ -232,6 +234,7 @@ constexpr int kScanMaxBlocks = 8192;               // supports scans of up to 8M
 void launch_grid(const DevPtrs& d, uint32_t max_row_hits, uint32_t max_pack_hits, hipStream_t s);
 void launch_links(const DevPtrs& d, uint32_t max_row_hits, hipStream_t s);
 void launch_clean_starts(const DevPtrs& d, uint32_t max_row_hits, hipStream_t s);
+hipError_t init_tracklets();   // with the device current, before the first launch_tracklets on it
 void launch_tracklets(const DevPtrs& d, const KfConst& k, uint32_t max_row_hits, hipStream_t s);
 void launch_select(const DevPtrs& d, const KfConst& k, uint32_t tile_rows, hipStream_t s);
 void launch_merge(const DevPtrs& d, const MergeArgs& m, uint32_t n_tracks, hipStream_t s);

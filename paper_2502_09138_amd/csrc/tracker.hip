@@ -477,6 +477,8 @@ tpc_status tpc_tracker_create(const tpc_tracker_config* cfg, tpc_tracker** out) 
   t->home_lay = lay;
   if (hipMemcpy((void*)t->d.rows, t->h_rows, R * sizeof(RowConst), hipMemcpyHostToDevice) != hipSuccess)
     return cleanup(fail(TPC_E_DEVICE, "upload row constants"));
+  if (const hipError_t e = init_tracklets(); e != hipSuccess)
+    return cleanup(fail(TPC_E_DEVICE, std::string("LDS limit of the tracklet kernels: ") + hipGetErrorString(e)));
   if (const tpc_status st = scratch_lookup(cfg->device); st != TPC_OK) return cleanup(st);
   if (hipEventCreateWithFlags(&t->done, hipEventDisableTiming) != hipSuccess)
     return cleanup(fail(TPC_E_DEVICE, "hipEventCreate"));
@@ -621,6 +623,12 @@ tpc_status enqueue(tpc_tracker* t, const tpc_timeframe* f, uint32_t max_row, uin
     c.inv_wz = (float)(1.0 / w);
     c.lz = (int32_t)std::ceil(10.0 * w);
     c.pad = 0;
+  }
+  d.max_sector_hits = d.res_blocks = 0;
+  for (uint32_t s = 0; s < S; ++s) {
+    const uint32_t n = f->row_offsets[(s + 1) * R] - f->row_offsets[s * R];
+    d.max_sector_hits = std::max(d.max_sector_hits, n);
+    d.res_blocks += (n + 16 * 128 - 1) / (16 * 128);
   }
   hipStream_t st = t->stream;   // the previous request was released, so the staging buffers are free
   if (f->flags & TPC_IN_HOST) {

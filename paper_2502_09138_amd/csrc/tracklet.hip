@@ -1236,6 +1236,392 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
   if (my_steps) atomicAdd(&d.hdr->n_steps, my_steps);
 }
 
+// ---------------------------------------------------------------------------
+// Row-synchronous schedule on resident sectors.  Where a whole sector fits in
+// the LDS of a compute unit (hits, bin starts, chain links and the row -> hit
+// columns of its workgroup's tracklets), a workgroup loads it once and its
+// waves sweep the rows without touching global memory and without barriers.
+// In k_tracklets_rs the next row's staging took about half of a row step: of
+// 4360 cycles on a pp frame 800 went into issuing its loads and 1400 into
+// waiting for them (a sector's few waves read each row first in their XCD, at
+// the latency of the last-level cache).
+//
+// Few tracklets leave the card idle, and the time is one wave's chain of
+// dependent steps, so kL lanes share a tracklet (2 .. 16: as many as keep every
+// wave alone on its SIMD): they test the candidates of a search side by side,
+// which makes each step shorter, and run the rest redundantly.
+//
+// Against k_tracklets_rs: a pp frame of one orbit 504 -> 334 us, of four orbits
+// 578 -> 413 us, one chunk of 5k hits 540 -> 330 us.
+constexpr int kResThreads = 256;
+constexpr uint32_t kResLdsBytes = 160u << 10;
+constexpr uint32_t kResPer = kResThreads / 2;   // tracklets of a workgroup, at two lanes each
+constexpr uint32_t kResRowHits = 254;  // a column holds a hit's place in its row in a byte
+constexpr uint32_t kNoHit = 255;
+constexpr uint32_t kNoLink = 0xFFFFu;
+constexpr uint32_t kRowTable = 32;     // bytes of a row in the row table: RowK, then a RowInfo
+
+// LDS of a sector of up to cap hits, its positions relative to the sector's first (16-bit): hits, row table, bin starts,
+// the columns of kResPer tracklets, and the links where there is room for them.
+struct ResLds {
+  uint32_t rows, bs, col, up, total;   // byte offsets; hits at 0; up 0: no links; total 0: the sector does not fit
+};
+inline ResLds res_lds(uint32_t cap, uint32_t max_row, uint32_t R, uint32_t hits_per_bin) {
+  auto up16 = [](uint32_t v) { return (v + 15u) & ~15u; };
+  ResLds l{};
+  if (cap >= kNoLink || max_row > kResRowHits) return l;
+  l.rows = up16(8 * cap);
+  l.bs = up16(l.rows + kRowTable * R);
+  l.col = up16(l.bs + 2 * (cap / hits_per_bin + 2 * R));
+  const uint32_t end = up16(l.col + R * kResPer), with_up = up16(end + 2 * cap);
+  if (end > kResLdsBytes) return l;
+  l.up = with_up <= kResLdsBytes ? end : 0u;
+  l.total = l.up ? with_up : end;
+  return l;
+}
+
+// A row in the row table; hits are named by their place, the sorted position less the sector's first.
+struct RowInfo {
+  uint32_t first, n, bins, dims;   // place of the first hit, hits, place of bin 0 among the bin starts, ny | nz << 16
+};
+struct RowEntry {
+  f32x4 k;
+  u32x4 i;
+};
+
+// Value of another lane of the kL lanes of a tracklet: a DPP move inside rows of 16.
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp_min(uint32_t v) {
+  return min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, kCtrl, 0xF, 0xF, false));
+}
+template <int kL>
+__device__ __forceinline__ uint32_t group_min(uint32_t v) {
+  if (kL >= 2) v = dpp_min<0xB1>(v);    // quad_perm 1,0,3,2
+  if (kL >= 4) v = dpp_min<0x4E>(v);    // quad_perm 2,3,0,1
+  if (kL >= 8) v = dpp_min<0x141>(v);   // row_half_mirror
+  if (kL >= 16) v = dpp_min<0x140>(v);  // row_mirror
+  return v;
+}
+
+// The search of C5 in a resident row: the place of the candidate closest to
+// the prediction, -1 if none.  Rows of few hits are tested whole; otherwise the
+// bins of the window, two z-lines at a time as one flat sequence (few-bin lines
+// all at once, see search_m).  The lanes of a tracklet take kU candidates in
+// turn; then the smallest deviation wins, ties to the smaller place.
+template <int kL>
+__device__ __forceinline__ int32_t search_row(const float2* yz, const uint16_t* bsec, const RowInfo& rr, const RowK& rk,
+                                              const SectorConst& sc, const Trk& t, const KfConst& k, float zref,
+                                              uint32_t sub) {
+  constexpr uint32_t kU = kL >= 8 ? 1 : kL == 4 ? 2 : 4;
+  const float sy2 = float(t.c[0] + k.vyd), sz2 = float(t.c[2] + k.vzd);
+  const float wy = fminf(k.gate * fsqrt(sy2), k.cap), wz = fminf(k.gate * fsqrt(sz2), k.cap);
+  const float isy = frcp(sy2), isz = frcp(sz2);
+  const float yp = float(t.p[0]), zp = float(t.p[1]);
+  uint32_t best = 0xFFFFFFFFu;
+  float bd = INFINITY;
+  // candidates lo0 .. lo0 + n0 - 1, then lo1 .., tot in all
+  auto test = [&](uint32_t lo0, uint32_t n0, uint32_t lo1, uint32_t tot) {
+    for (uint32_t f0 = sub * kU; f0 < tot; f0 += kL * kU) {
+      uint32_t pos[kU];
+      float2 h[kU];
+#pragma unroll
+      for (uint32_t j = 0; j < kU; ++j) {
+        const uint32_t f = min(f0 + j, tot - 1);
+        pos[j] = f < n0 ? lo0 + f : lo1 + (f - n0);
+        h[j] = yz[pos[j]];
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < kU; ++j) {   // a clamped place is tested twice, which changes nothing
+        const float dy = h[j].x - yp, dz = (h[j].y - zref) - zp;
+        const float dd = __builtin_fmaf(dy * dy, isy, (dz * dz) * isz);
+        const bool take = fabsf(dy) <= wy & fabsf(dz) <= wz & dd < bd;
+        best = take ? pos[j] : best;
+        bd = take ? dd : bd;
+      }
+    }
+  };
+  if (rr.n <= 2 * kL * kU) {   // wave-uniform
+    if (rr.n) test(rr.first, rr.n, 0u, rr.n);
+  } else {
+    const float za = zref + zp;
+    const int ny = (int)(rr.dims & 0xFFFFu), nz = (int)(rr.dims >> 16);
+    const int iy0 = bin1((yp - wy) - kWinPad, rk.y_lo, rk.inv_wy, ny);
+    const int iy1 = bin1((yp + wy) + kWinPad, rk.y_lo, rk.inv_wy, ny);
+    const int iz0 = bin1((za - wz) - kWinPad, sc.z_lo, sc.inv_wz, nz);
+    const int iz1 = bin1((za + wz) + kWinPad, sc.z_lo, sc.inv_wz, nz);
+    const uint16_t* bs = bsec + rr.bins;
+    if (ny <= kRunBins) {
+      const uint32_t lo = bs[iz0 * ny + iy0], n = bs[iz1 * ny + iy1 + 1] - lo;
+      test(lo, n, 0u, n);
+    } else {
+      for (int iz = iz0; iz <= iz1; iz += 2) {
+        const int izb = iz + 1 <= iz1 ? iz + 1 : iz;
+        const uint32_t lo0 = bs[iz * ny + iy0], n0 = bs[iz * ny + iy1 + 1] - lo0;
+        const uint32_t lo1 = bs[izb * ny + iy0], n1 = bs[izb * ny + iy1 + 1] - lo1;
+        test(lo0, n0, lo1, n0 + (izb > iz ? n1 : 0u));
+      }
+    }
+  }
+  // deviations are not negative, so their bits order as they do
+  const uint32_t mine = (uint32_t)__float_as_int(bd), least = group_min<kL>(mine);
+  return (int32_t)group_min<kL>(mine == least ? best : 0xFFFFFFFFu);
+}
+
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane(v); }
+
+// A sector in LDS.
+struct Resident {
+  const float2* yz;
+  const f32x4* rows;         // the row table
+  const uint16_t *bs, *up;   // bin starts; links (nullptr: not resident)
+  uint32_t a0;               // the sector's first sorted position
+
+  // A row is the same for the whole wave; its entry is read a step before it is needed (into vector registers, no wait)
+  // and moved to scalar registers then.  Scalar loads would not do: they share a counter with LDS reads but return out of
+  // order, so the step's first LDS read would wait for them.
+  __device__ __forceinline__ RowEntry entry(uint32_t r) const {
+    return RowEntry{rows[2 * r], *reinterpret_cast<const u32x4*>(rows + 2 * r + 1)};
+  }
+  __device__ __forceinline__ float x(uint32_t r) const { return reinterpret_cast<const float*>(rows + 2 * r)[0]; }
+  __device__ __forceinline__ uint32_t first(uint32_t r) const {
+    return reinterpret_cast<const uint32_t*>(rows + 2 * r + 1)[0];
+  }
+  // the place after p in its chain, kNoLink at its end
+  __device__ __forceinline__ uint32_t next(const DevPtrs& d, uint32_t p) const {
+    if (up) return up[p];
+    const int32_t u = d.up1[a0 + p];
+    return u >= 0 ? (uint32_t)u - a0 : kNoLink;
+  }
+};
+__device__ __forceinline__ RowK row_k(const RowEntry& e) {
+  return RowK{uniform_f(e.k.x), uniform_f(e.k.y), uniform_f(e.k.z), uniform_f(e.k.w)};
+}
+__device__ __forceinline__ RowInfo row_info(const RowEntry& e) {
+  return RowInfo{uniform(e.i.x), uniform(e.i.y), uniform(e.i.z), uniform(e.i.w)};
+}
+
+// Chain, seed and both sweeps of tracklet i, kL lanes; returns its row steps on
+// the lane that writes.  col[r * kPer] is the hit in row r, as its place in the
+// row.
+template <int kL, uint32_t kPer>
+__device__ __forceinline__ uint32_t sweep(const DevPtrs& d, const KfConst& k, const Resident& S, uint8_t* col, uint32_t sec,
+                                          uint32_t i, uint32_t te) {
+  const uint32_t R = d.R, T = d.tcap, sub = threadIdx.x % kL;
+  const bool writes = sub == 0;   // of the lanes of a tracklet, which hold the same
+  const SectorConst sc = d.secs[sec];
+  bool ok = i < te;
+  uint32_t r0 = 0, rl = 0, n = 0;
+  float zref = 0.0f, chi2 = 0.0f, xprev = 0.0f;
+  Trk t;
+  if (ok) {
+    r0 = d.start_sr[i] - sec * R;
+    const uint32_t p0 = d.start_pos[i] - S.a0;
+    // chain walk: its rows of the column and, following at half the speed, its middle hit
+    uint32_t p = p0, last = p0, mid = p0;
+    while (p != kNoLink && r0 + n < R) {
+      last = p;
+      if (writes) col[(r0 + n) * kPer] = (uint8_t)(p - S.first(r0 + n));
+      if (n && n % 2 == 0) mid = S.next(d, mid);
+      p = S.next(d, p);
+      ++n;
+    }
+    rl = r0 + n - 1;
+    const float2 h0 = S.yz[p0];
+    zref = h0.y;
+    if (seed3(S.x(r0), h0, S.x(r0 + (n - 1) / 2), S.yz[mid], S.x(rl), S.yz[last], k, t)) {
+      set_c0(t, k);
+      xprev = S.x(r0);
+    } else {
+      if (writes) d.tk_info[i] = -1;
+      ok = false;
+    }
+  }
+  uint32_t steps = ok ? n - 1 : 0;
+  // ---- outward sweep ----
+  bool up = ok, failed = false;
+  par_t pout[3] = {t.p[2], t.p[3], t.p[4]};
+  uint32_t rout = rl;
+  int miss = 0;
+  uint32_t r = uniform(wave_min(up ? r0 + 1 : R));
+  RowEntry next = S.entry(r < R ? r : 0);
+  uint32_t hnext = r < R ? col[r * kPer] : kNoHit;   // used only in chain rows
+  for (; r < R && __any(up); ++r) {
+    const RowInfo row = row_info(next);
+    const RowK rk = row_k(next);
+    const uint32_t hchain = hnext, rn = r + 1 < R ? r + 1 : r;
+    next = S.entry(rn);
+    hnext = col[rn * kPer];
+    if (up && r > r0) {
+      const bool chain = r <= rl;
+      steps += chain ? 0u : 1u;
+      const bool pok = propagate<true>(t, rk.x - xprev, k);
+      xprev = rk.x;
+      failed = failed || (!pok && chain);
+      const bool go = pok && (chain || fabs_(t.p[0]) <= rk.half_y + k.margin);
+      up = go;
+      int32_t h = chain ? (int32_t)(row.first + hchain) : -1;
+      if (go && !chain) {
+        h = search_row<kL>(S.yz, S.bs, row, rk, sc, t, k, zref, sub);
+        if (writes) col[r * kPer] = (uint8_t)(h >= 0 ? (uint32_t)h - row.first : kNoHit);
+      }
+      if (go && h >= 0) {
+        const float2 hm = S.yz[h];
+        update(t, hm.x, hm.y - zref, k, chi2);
+        if (r >= rl) {
+#pragma unroll
+          for (int q = 0; q < 3; ++q) pout[q] = t.p[2 + q];
+          rout = r;
+          miss = 0;
+        }
+      }
+      const bool missed = go && h < 0;
+      miss += missed ? 1 : 0;
+      up = up && !(missed && miss > k.max_miss);
+    }
+  }
+  if (failed) {
+    if (writes) d.tk_info[i] = -2;
+    ok = false;
+  }
+  // ---- inward sweep from each lane's outermost hit, fresh covariance ----
+  bool down = ok;
+  int nh = 1;
+  Snap snap;
+  uint32_t rin = rout;
+  if (down) {
+    const float2 ho = S.yz[S.first(rout) + col[rout * kPer]];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) t.p[2 + q] = pout[q];
+    t.p[0] = ho.x;
+    t.p[1] = ho.y - zref;
+    set_c0(t, k);
+    chi2 = 0.0f;
+    snap = snap_of(t);
+    xprev = S.x(rout);
+    miss = 0;
+  }
+  int32_t q = (int32_t)uniform(wave_max(down ? rout : 0)) - 1;
+  next = S.entry(q >= 0 ? (uint32_t)q : 0);
+  hnext = q >= 0 ? col[(uint32_t)q * kPer] : kNoHit;   // used only in [r0, rout)
+  for (; q >= 0 && __any(down); --q) {
+    const RowInfo row = row_info(next);
+    const RowK rk = row_k(next);
+    const uint32_t hrow = hnext, qn = q > 0 ? (uint32_t)q - 1 : 0;
+    next = S.entry(qn);
+    hnext = col[qn * kPer];
+    if (down && q < (int32_t)rout) {
+      ++steps;
+      const bool pok = propagate<true>(t, rk.x - xprev, k);
+      xprev = rk.x;
+      const bool below = (uint32_t)q < r0;
+      const bool go = pok && !(below && fabs_(t.p[0]) > rk.half_y + k.margin);
+      down = go;
+      int32_t h = below || hrow == kNoHit ? -1 : (int32_t)(row.first + hrow);
+      if (go && h < 0) {
+        h = search_row<kL>(S.yz, S.bs, row, rk, sc, t, k, zref, sub);
+        if (writes) col[(uint32_t)q * kPer] = (uint8_t)(h >= 0 ? (uint32_t)h - row.first : kNoHit);
+      }
+      if (go && h >= 0) {
+        const float2 hm = S.yz[h];
+        update(t, hm.x, hm.y - zref, k, chi2);
+        ++nh;
+        snap = snap_of(t);
+        rin = (uint32_t)q;
+        if (below) miss = 0;
+      }
+      const bool missed = go && below && h < 0;
+      miss += missed ? 1 : 0;
+      down = down && !(missed && miss > k.max_miss);
+    }
+  }
+  if (!ok) return 0;
+  int32_t* H = d.tk_rowhit + i;     // the column's rows that the selector reads
+  for (uint32_t w = rin + sub; w <= rout; w += kL) {
+    const uint32_t h = col[w * kPer];
+    H[(size_t)w * T] = h == kNoHit ? -1 : (int32_t)(S.a0 + S.first(w) + h);
+  }
+  if (!writes) return 0;
+  store_tracklet<true>(d, i, nh, rin, rout, r0, snap, chi2, zref);
+  return steps;
+}
+
+template <int kL>
+__device__ __forceinline__ void resident_sector(const DevPtrs& d, const KfConst& k, const ResLds& l, unsigned char* lds,
+                                                uint32_t sec, uint32_t part, uint32_t parts) {
+  constexpr uint32_t kPer = kResThreads / kL;   // tracklets per workgroup
+  const uint32_t R = d.R, T = d.tcap, tid = threadIdx.x, srb = sec * R;
+  const uint32_t ts = min(d.row_start_off[srb], T), te = min(d.row_start_off[srb + R], T);
+  if (ts + part * kPer >= te) return;   // the grid is sized without the number of tracklets
+  float2* yz = reinterpret_cast<float2*>(lds);
+  f32x4* rows = reinterpret_cast<f32x4*>(lds + l.rows);
+  uint16_t* bs = reinterpret_cast<uint16_t*>(lds + l.bs);
+  uint16_t* up = l.up ? reinterpret_cast<uint16_t*>(lds + l.up) : nullptr;
+  const uint32_t a0 = d.row_off[srb], n_hits = d.row_off[srb + R] - a0;
+  // in batches whose loads are all out before the first is written to LDS
+  constexpr uint32_t kU = 8;
+  for (uint32_t q0 = tid; q0 < n_hits; q0 += kU * kResThreads) {
+    float2 h[kU];
+    int32_t u[kU];
+#pragma unroll
+    for (uint32_t j = 0; j < kU; ++j) {
+      const uint32_t q = a0 + min(q0 + j * kResThreads, n_hits - 1);
+      h[j] = d.syz[q];
+      u[j] = up ? d.up1[q] : -1;
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kU; ++j) {
+      const uint32_t q = q0 + j * kResThreads;
+      if (q >= n_hits) break;
+      yz[q] = h[j];
+      if (up) up[q] = (uint16_t)(u[j] >= 0 ? (uint32_t)u[j] - a0 : kNoLink);
+    }
+  }
+  // row table and bin starts, 16 lanes a row; a row's n / K bins and their end fit between first / K + 2 r of this row
+  // and of the next
+  for (uint32_t r = tid / 16; r < R; r += kResThreads / 16) {
+    const RowConst rc = d.rows[r];
+    const uint32_t o = d.row_off[srb + r], n = d.row_off[srb + r + 1] - o, lane = tid % 16;
+    const uint2 m = d.row_meta[srb + r];
+    const uint32_t at = (o - a0) / (uint32_t)d.grid_k + 2 * r, nb = (m.y & 0xFFFFu) * (m.y >> 16);
+    if (lane == 0) {
+      rows[2 * r] = f32x4{rc.x, rc.half_y, rc.y_lo, rc.inv_wy};
+      *reinterpret_cast<u32x4*>(rows + 2 * r + 1) = u32x4{o - a0, n, at, m.y};
+    }
+    for (uint32_t b0 = lane; b0 <= nb; b0 += 16 * kU) {
+      uint32_t v[kU];
+#pragma unroll
+      for (uint32_t j = 0; j < kU; ++j) v[j] = d.bin_start[m.x + min(b0 + 16 * j, nb)];
+#pragma unroll
+      for (uint32_t j = 0; j < kU; ++j)
+        if (b0 + 16 * j <= nb) bs[at + b0 + 16 * j] = (uint16_t)(v[j] - a0);
+    }
+  }
+  __syncthreads();
+  const Resident S{yz, rows, bs, up, a0};
+  uint32_t steps = 0;   // of all its tracklets: at most 2^23 of 510 steps over the frame
+  for (uint32_t i0 = ts + part * kPer; i0 < te; i0 += parts * kPer)   // workgroup-uniform
+    steps += sweep<kL, kPer>(d, k, S, lds + l.col + tid / kL, sec, i0 + tid / kL, te);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) steps += (uint32_t)__shfl_xor((int)steps, off, kWave);
+  if (tid % kWave == 0 && steps) atomicAdd(&d.hdr->n_steps, (unsigned long long)steps);
+}
+
+// Lanes for a wave on each of the 1024 SIMDs; a quarter goes to workgroups that are not full.
+constexpr uint32_t kLanesAlone = 1024u * kWave * 3 / 4;
+
+__global__ void __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(3)))
+k_tracklets_res(DevPtrs d, KfConst k, ResLds l, uint32_t parts) {
+  extern __shared__ __align__(16) unsigned char res_s[];
+  // the first part of every sector, then the second and so on: the workgroups without tracklets come last, and the others
+  // spread over the XCDs and CUs
+  const uint32_t sec = blockIdx.x % d.S, part = blockIdx.x / d.S;
+  const uint32_t n = min(d.hdr->n_starts, d.tcap);
+  if (n * 16 <= kLanesAlone) resident_sector<16>(d, k, l, res_s, sec, part, parts);
+  else if (n * 8 <= kLanesAlone) resident_sector<8>(d, k, l, res_s, sec, part, parts);
+  else if (n * 4 <= kLanesAlone) resident_sector<4>(d, k, l, res_s, sec, part, parts);
+  else resident_sector<2>(d, k, l, res_s, sec, part, parts);
+}
+
 // Waves of the row-synchronous schedule: ceil(tracklets of sector s / 32) per
 // sector, prefix-summed (one block).
 __global__ void __launch_bounds__(1024) k_waves(DevPtrs d) {
@@ -1260,9 +1646,24 @@ __global__ void __launch_bounds__(1024) k_waves(DevPtrs d) {
 
 }  // namespace
 
+// Once per device: the resident kernel takes more dynamic LDS than the default limit.
+hipError_t init_tracklets() {
+  return hipFuncSetAttribute((const void*)k_tracklets_res, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResLdsBytes);
+}
+
 void launch_tracklets(const DevPtrs& d, const KfConst& k, uint32_t max_row_hits, hipStream_t s) {
   if (d.tcap == 0) return;
   const bool rowsync = d.k5_mode == 2 || (d.k5_mode == 0 && max_row_hits <= (uint32_t)kStageHits);
+  // Resident sectors while their workgroups run side by side (three on a CU at most, by registers; about a tracklet per 16
+  // hits): 60 chunks of up to 13k hits run 7% faster than row by row, 500 of up to 3k as fast, and 400 of up to 13k, one
+  // workgroup on a CU at a time, 2.3 times as long.
+  const ResLds l = res_lds(std::max(1u, d.max_sector_hits), max_row_hits, d.R, (uint32_t)d.grid_k);
+  if (d.k5_mode != 1 && l.total && d.res_blocks <= 256u * std::min(3u, kResLdsBytes / l.total)) {
+    // a sector with more tracklets than its parts hold loops
+    const uint32_t parts = std::max((768u + d.S - 1) / d.S, (d.max_sector_hits / 16 + kResPer - 1) / kResPer);
+    hipLaunchKernelGGL(k_tracklets_res, dim3(d.S * parts), dim3(kResThreads), l.total, s, d, k, l, parts);
+    return;
+  }
   if (rowsync) {
     hipLaunchKernelGGL(k_waves, dim3(1), dim3(1024), 0, s, d);
     uint32_t blocks = (d.tcap + kTrkPerWave - 1) / kTrkPerWave + d.S;

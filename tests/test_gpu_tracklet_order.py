@@ -32,3 +32,39 @@ def test_wave_order_changes_nothing(kind, size):
         assert other.n_tracklets == got[0].n_tracklets
         for k in FIELDS:
             np.testing.assert_array_equal(getattr(got[0], k), getattr(other, k), err_msg=k)
+
+
+@pytest.mark.parametrize("kind, size", [("event", (1, 2)), ("event", (1, 45)), ("event", (2, 100)), ("event", (36, 12)),
+                                        ("event", (36, 80)), ("chunks", 90), ("pp", 4)])
+def test_resident_sectors_change_nothing(kind, size):
+    """Frames whose sectors are swept resident in LDS (from two tracks, 16 lanes a tracklet, to sectors of about 13k
+    hits, two lanes and no room for the links; chunks of very uneven sizes) against the lane-per-tracklet pipeline, bit
+    for bit, row -> hit columns included."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2502_09138_amd import tracker as T
+    if kind == "event":
+        ev = synth.single_sector(seed=3, n_tracks=size[1]) if size[0] == 1 else \
+            synth.central_event(seed=4, n_primaries=size[1] * 36, sectors=range(size[0]))
+    else:
+        ev = synth.uneven_chunks(chunks=range(size), n_max=6000) if kind == "chunks" else \
+            synth.pp_time_frame(seed=54, n_orbits=size)
+    print("case: resident sectors", kind, size, "N=", ev.n_clusters, "largest sector",
+          int(np.diff(ev.row_offsets[::synth.N_ROWS].astype(np.int64)).max()), flush=True)
+    tr = T.Tracker(default_config(), max_clusters=ev.n_clusters, max_sectors=ev.n_sectors)
+    got = []
+    for schedule in (2, 1):
+        tr.set_knobs(schedule=schedule)
+        out = tr.track_event(ev, host=True)
+        info = tr.debug(T.TPC_DBG_TK_INFO, np.int32).reshape(4, -1)[:, :out.n_tracklets]
+        col = tr.debug(T.TPC_DBG_TK_ROWHIT, np.int32).reshape(synth.N_ROWS, -1)[:, :out.n_tracklets]
+        row = np.arange(synth.N_ROWS)[:, None]
+        held = (info[0] > 0) & (row >= info[1]) & (row <= info[2])
+        got.append((out, info[0], np.where(info[0] > 0, info, 0), np.where(held, col, -2)))
+    tr.close()
+    assert got[0][0].n_tracklets == got[1][0].n_tracklets > 0
+    for k in FIELDS:
+        np.testing.assert_array_equal(getattr(got[0][0], k), getattr(got[1][0], k), err_msg=k)
+    for a, b in zip(got[0][1:], got[1][1:]):
+        np.testing.assert_array_equal(a, b)
