@@ -80,10 +80,51 @@ __global__ void __launch_bounds__(kThreads) k_scan_down(const T* in, T* out, uin
   }
 }
 
+// The whole scan by one workgroup, a tile of 4096 elements at a time.
+constexpr int kOneThreads = 1024;
+constexpr int kOneItems = 4;
+template <typename T>
+__global__ void __launch_bounds__(kOneThreads) k_scan_one(const T* in, T* out, uint32_t n, const uint32_t* n_dev,
+                                                          uint32_t n_max) {
+  __shared__ T wsum[kOneThreads / kWave];
+  const uint32_t cnt = scan_count<T>(n, n_dev, n_max);
+  T before = 0;
+  for (uint32_t base = 0; base < cnt; base += kOneThreads * kOneItems) {
+    T v[kOneItems], s = 0;
+#pragma unroll
+    for (int k = 0; k < kOneItems; ++k) {
+      const uint32_t i = base + threadIdx.x * kOneItems + k;
+      v[k] = i < cnt ? in[i] : (T)0;
+      s += v[k];
+    }
+    T total;
+    T run = before + block_exclusive_scan<T>(s, wsum, &total);
+#pragma unroll
+    for (int k = 0; k < kOneItems; ++k) {
+      const uint32_t i = base + threadIdx.x * kOneItems + k;
+      if (i < cnt) out[i] = run;
+      run += v[k];
+    }
+    before += total;
+  }
+  if (threadIdx.x == 0) out[cnt] = before;
+}
+
+// One launch instead of three up to this many elements (where the number is on the device: up to this capacity, of which
+// a frame fills about a fifth).  Bound: the launches, not the elements, as long as the tiles are few: 4 here, a round of
+// loads each.  With the header's own launch and copies gone too, a
+// 5k-hit chunk went from 509 to 484 us, a sector of 27k from 734 to 716, a pp frame of one orbit from 595 to 553.
+constexpr uint32_t kOneMax = 16384;
+constexpr uint32_t kOneMaxDev = 65536;
+
 template <typename T>
 void scan_impl(const T* in, T* out, uint32_t n, const uint32_t* n_dev, uint32_t n_max, unsigned long long* blocks,
                hipStream_t s) {
   const uint32_t span = n_dev ? n_max : n;
+  if (span <= (n_dev ? kOneMaxDev : kOneMax)) {
+    hipLaunchKernelGGL(k_scan_one<T>, dim3(1), dim3(kOneThreads), 0, s, in, out, n, n_dev, n_max);
+    return;
+  }
   const uint32_t nb = span == 0 ? 1 : (span + kScanBlock - 1) / kScanBlock;
   hipLaunchKernelGGL(k_scan_reduce<T>, dim3(nb), dim3(kThreads), 0, s, in, n, n_dev, n_max, blocks);
   hipLaunchKernelGGL(k_scan_blocks<T>, dim3(1), dim3(1024), 0, s, blocks, n, n_dev, n_max);

@@ -179,6 +179,7 @@ __global__ void __launch_bounds__(kThreads) k_accept(DevPtrs d, KfConst k, uint3
 template <int kT>
 __global__ void __launch_bounds__(kT) k_emit_tiles(DevPtrs d, KfConst k, uint32_t tile_rows, uint32_t n_tiles) {
   extern __shared__ uint32_t wt[];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *d.hdr_host = *d.hdr;   // complete since k_records
   const uint32_t v = tile_index(d, n_tiles);
   if (v >= d.S * n_tiles) return;
   const Tile tl = tile_of(d, v, tile_rows, n_tiles);
@@ -249,9 +250,16 @@ __device__ __forceinline__ void finish(const DevPtrs& d) {
   if (!flags) d.out_first[ntr] = (uint32_t)ncl;
 }
 
-__global__ void __launch_bounds__(kThreads) k_records(DevPtrs d, KfConst k) {
+// last: the selection's last kernel, which also writes the header to the host.
+__global__ void __launch_bounds__(kThreads) k_records(DevPtrs d, KfConst k, bool last) {
   const uint32_t nt = n_tracklets(d), T = d.tcap;
-  if (blockIdx.x == 0 && threadIdx.x == 0) finish(d);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    finish(d);
+    if (last) {
+      __threadfence();   // the flags go through an atomic
+      *d.hdr_host = *d.hdr;
+    }
+  }
   const XcdSched sch = xcd_sched(nt);
   for (uint32_t vb = sch.first; vb < sch.end; vb += sch.stride) {
     const uint32_t i = vb * blockDim.x + threadIdx.x;
@@ -369,7 +377,7 @@ void launch_select(const DevPtrs& d, const KfConst& k, uint32_t tile_rows, hipSt
     else hipLaunchKernelGGL(k_claim_tiles<512>, tiles, dim3(nt), lds, s, d, k, tile_rows, n_tiles);
     hipLaunchKernelGGL(k_accept, dim3(blocks), dim3(kThreads), 0, s, d, k, tile_rows);
     launch_scan_u64(d.tk_pack, d.tk_scan, &d.hdr->n_starts, d.tcap, d.scan_blocks, s);
-    hipLaunchKernelGGL(k_records, dim3(blocks), dim3(kThreads), 0, s, d, k);
+    hipLaunchKernelGGL(k_records, dim3(blocks), dim3(kThreads), 0, s, d, k, false);
     if (nt == 1024) hipLaunchKernelGGL(k_emit_tiles<1024>, tiles, dim3(nt), lds, s, d, k, tile_rows, n_tiles);
     else if (nt == 256) hipLaunchKernelGGL(k_emit_tiles<256>, tiles, dim3(nt), lds, s, d, k, tile_rows, n_tiles);
     else hipLaunchKernelGGL(k_emit_tiles<512>, tiles, dim3(nt), lds, s, d, k, tile_rows, n_tiles);
@@ -380,7 +388,7 @@ void launch_select(const DevPtrs& d, const KfConst& k, uint32_t tile_rows, hipSt
     hipLaunchKernelGGL(k_own_g, dim3(blocks), dim3(kThreads), 0, s, d, k);
     launch_scan_u64(d.tk_pack, d.tk_scan, &d.hdr->n_starts, d.tcap, d.scan_blocks, s);
     hipLaunchKernelGGL(k_emit_g, dim3(blocks), dim3(kThreads), 0, s, d, k);
-    hipLaunchKernelGGL(k_records, dim3(blocks), dim3(kThreads), 0, s, d, k);
+    hipLaunchKernelGGL(k_records, dim3(blocks), dim3(kThreads), 0, s, d, k, true);
   }
 }
 

@@ -44,7 +44,7 @@ struct KfConst {
   int32_t n_rows;
 };
 
-// Device result header (copied to pinned host memory at the end of a request).
+// Device result header (cleared with the frame's metadata, written to pinned host memory at the end of a request).
 struct ResultHeader {
   uint32_t n_starts;       // C4 count (may exceed capacity; see flags)
   uint32_t error_flags;
@@ -117,6 +117,7 @@ struct DevPtrs {
   // scratch for scans
   unsigned long long* scan_blocks;   // [kScanMaxBlocks]
   ResultHeader* hdr;
+  ResultHeader* hdr_host;    // its pinned host copy, written by the request's last kernel
   // sizes
   int32_t grid_k;
   float rho;                 // (sigma_y / sigma_z)^2, float32
