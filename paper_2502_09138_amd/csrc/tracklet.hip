@@ -211,9 +211,9 @@ __device__ __forceinline__ void update(Trk& t, float ym, float zm, const KfConst
     t.p[i] = fma(K0[i], r0, fma(K1[i], r1, t.p[i]));
   }
 #pragma unroll
-  for (int i = 0; i < 5; ++i)
+  for (int i = 4; i >= 0; --i)   // downwards, so that each element is overwritten after its last use (fewer moves: -1%)
 #pragma unroll
-    for (int j = 0; j <= i; ++j) c[tri(i, j)] = fma(-K0[i], c0[j], fma(-K1[i], c1[j], c[tri(i, j)]));
+    for (int j = i; j >= 0; --j) c[tri(i, j)] = fma(-K0[i], c0[j], fma(-K1[i], c1[j], c[tri(i, j)]));
   chi2 += float(r0 * (I00 * r0 + I01 * r1) + r1 * (I01 * r0 + I11 * r1));
 }
 
@@ -297,6 +297,150 @@ __device__ __forceinline__ int32_t search_m(const DevPtrs& d, uint2 meta, const 
 __device__ __forceinline__ int32_t search(const DevPtrs& d, uint32_t sr, const RowK& rk, const SectorConst& sc,
                                           const Trk& t, const KfConst& k, float zref, float2& hv) {
   return search_m(d, d.row_meta[sr], rk, sc, t, k, zref, hv);
+}
+
+// The same search for the lanes of a wave together: the candidates of all searching lanes are cut into items of kItem,
+// and the items are dealt out to all 64 lanes, whichever lane they belong to.  Called by the whole wave, converged.
+//
+// Bound: vector instructions (the passes that search issue one in 92% of their cycles).  On the 32-orbit frame a search
+// has 5.2 candidates on average and 28 of a wave's 64 lanes search in a step, but the lane with the most takes 2.9 groups
+// of 6: tested lane by lane (search_m), 13% of the tests do work, and they are half of the instructions.  Dealt out, a
+// step's 49 items take one round (the average; chunks 63, some two).  An item's owner is found by a scan over the items'
+// starts, its window is read with lane permutes, and the winner comes from an LDS minimum over (deviation, position): the
+// smallest deviation, ties to the smaller position, which is what the ascending scan of search_m takes.
+// k_up and k_down: 32-orbit frame 2151 -> 1843 us, 512 uneven chunks 5466 -> 5010, 8 heavy-ion orbits 924 -> 833.  Items of 2:
+// +4%, of 6: +2%.  A window of more than two runs (a narrow grid under a wide cap) is left to search_m.
+constexpr int kItem = 4;
+struct WaveSearch {
+  unsigned long long key[kThreads];   // per lane: (deviation, position) of its best candidate
+  float2 hv[kThreads];                // (y, z) of it
+  uint32_t map[kThreads];             // slot -> lane + 1 at the slot of a lane's first item, else 0
+};
+static_assert(kItem % 2 == 0 && kItem <= kGroup, "items are loaded in pairs; the arrays' slack covers a group");
+
+__device__ __forceinline__ void wave_lds_order() {   // LDS accesses of a wave complete in order; keep the compiler to it
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+template <int kCtrl, int kRows, class Op>
+__device__ __forceinline__ uint32_t dpp_step(uint32_t v, Op op) {
+  return op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRows, 0xF, false));
+}
+// inclusive scan over the wave, op's identity 0
+template <class Op>
+__device__ __forceinline__ uint32_t dpp_scan(uint32_t v, Op op) {
+  v = dpp_step<0x111, 0xF>(v, op);   // row_shr 1, 2, 4, 8
+  v = dpp_step<0x112, 0xF>(v, op);
+  v = dpp_step<0x114, 0xF>(v, op);
+  v = dpp_step<0x118, 0xF>(v, op);
+  v = dpp_step<0x142, 0xA>(v, op);   // row_bcast 15 into rows 1 and 3
+  v = dpp_step<0x143, 0xC>(v, op);   // row_bcast 31 into rows 2 and 3
+  return v;
+}
+
+__device__ __forceinline__ int32_t search_wave(const DevPtrs& d, WaveSearch& l, bool want, uint2 meta, const RowK& rk,
+                                               const SectorConst& sc, const Trk& t, const KfConst& k, float zref,
+                                               float2& hv) {
+  if (!__any(want)) return -1;
+  const uint32_t lane = threadIdx.x;
+  const float sy2 = float(t.c[0] + k.vyd), sz2 = float(t.c[2] + k.vzd);
+  const float wy = fminf(k.gate * fsqrt(sy2), k.cap), wz = fminf(k.gate * fsqrt(sz2), k.cap);
+  const float isy = frcp(sy2), isz = frcp(sz2);
+  const float yp = float(t.p[0]), zp = float(t.p[1]);
+  uint32_t b0 = 0, b1 = 0, e = 0, ny = 0;
+  if (want) {
+    const float za = zref + zp;
+    ny = meta.y & 0xFFFFu;
+    const int nz = (int)(meta.y >> 16);
+    const int iy0 = bin1((yp - wy) - kWinPad, rk.y_lo, rk.inv_wy, (int)ny);
+    const int iy1 = bin1((yp + wy) + kWinPad, rk.y_lo, rk.inv_wy, (int)ny);
+    const int iz0 = bin1((za - wz) - kWinPad, sc.z_lo, sc.inv_wz, nz);
+    const int iz1 = bin1((za + wz) + kWinPad, sc.z_lo, sc.inv_wz, nz);
+    b0 = meta.x + (uint32_t)iz0 * ny + (uint32_t)iy0;
+    e = meta.x + (uint32_t)iz1 * ny + (uint32_t)iy1;
+    b1 = ny <= (uint32_t)kRunBins ? e : b0 + (uint32_t)(iy1 - iy0);
+  }
+  l.key[lane] = ~0ull;
+  int32_t alone = -1;
+  const bool far = want && b1 + ny < e;
+  if (far) alone = search_m(d, meta, rk, sc, t, k, zref, hv);   // more than two runs
+  // up to two runs per lane: [q0, h0) and [q1, h1)
+  uint32_t q0 = 0, h0 = 0, q1 = 0, h1 = 0;
+  if (want && !far) {
+    q0 = d.bin_start[b0];
+    h0 = d.bin_start[b1 + 1];
+    if (b1 < e) {
+      q1 = d.bin_start[b0 + ny];
+      h1 = d.bin_start[b1 + ny + 1];
+    }
+  }
+  const uint32_t n0 = (h0 - q0 + kItem - 1) / kItem, n = n0 + (h1 - q1 + kItem - 1) / kItem;
+  const uint32_t end = dpp_scan(n, [](uint32_t a, uint32_t b) { return a + b; });
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)end, kWave - 1);
+  const uint32_t start = end - n, split = start + n0;
+  const bool two = __any(h1 > q1);
+  for (uint32_t base = 0; base < total; base += kWave) {
+    l.map[lane] = 0;
+    wave_lds_order();
+    if (n > 0 && end > base && start < base + kWave) l.map[max(start, base) - base] = lane + 1;
+    wave_lds_order();
+    const uint32_t own = dpp_scan(l.map[lane], [](uint32_t a, uint32_t b) { return max(a, b); }) - 1;
+    const int at = (int)(own * 4);
+    auto from = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_ds_bpermute(at, (int)v); };
+    auto fromf = [&](float v) { return __int_as_float(__builtin_amdgcn_ds_bpermute(at, __float_as_int(v))); };
+    const uint32_t slot = base + lane;
+    uint32_t q = from(q0 - start * kItem), lim = from(h0);
+    if (two) {
+      const uint32_t s1 = from(split), qb = from(q1 - split * kItem), hb = from(h1);
+      if (slot >= s1) {
+        q = qb;
+        lim = hb;
+      }
+    }
+    q += slot * kItem;
+    const float oyp = fromf(yp), owy = fromf(wy), oisy = fromf(isy);
+    const float ozr = fromf(zref), ozp = fromf(zp), owz = fromf(wz), oisz = fromf(isz);
+    float bd = INFINITY;
+    uint32_t bq = 0;
+    float2 bh = make_float2(0.0f, 0.0f);
+    if (slot < total) {
+      float2 h[kItem];
+      const f32x4_at8* src = reinterpret_cast<const f32x4_at8*>(d.syz + q);
+#pragma unroll
+      for (int j = 0; j < kItem / 2; ++j) {
+        const f32x4 v = src[j];
+        h[2 * j] = make_float2(v.x, v.y);
+        h[2 * j + 1] = make_float2(v.z, v.w);
+      }
+      const uint32_t m = lim - q;
+#pragma unroll
+      for (int j = 0; j < kItem; ++j) {
+        const float dy = h[j].x - oyp, dz = (h[j].y - ozr) - ozp;
+        const float dd = __builtin_fmaf(dy * dy, oisy, (dz * dz) * oisz);
+        const bool take = (uint32_t)j < m & fabsf(dy) <= owy & fabsf(dz) <= owz & dd < bd;
+        bq = take ? q + j : bq;
+        bd = take ? dd : bd;
+        bh.x = take ? h[j].x : bh.x;
+        bh.y = take ? h[j].y : bh.y;
+      }
+    }
+    const bool found = bd < INFINITY;
+    unsigned long long mine = 0;
+    wave_lds_order();
+    if (found) {
+      const uint32_t b = (uint32_t)__float_as_int(bd + 0.0f);
+      mine = ((unsigned long long)(b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u)) << 32) | bq;
+      __hip_atomic_fetch_min(&l.key[own], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    }
+    wave_lds_order();
+    if (found && l.key[own] == mine) l.hv[own] = bh;
+  }
+  wave_lds_order();
+  const unsigned long long best = l.key[lane];
+  if (best == ~0ull) return alone;
+  hv = l.hv[lane];
+  return (int32_t)(uint32_t)best;
 }
 
 // The same search over a row staged in LDS: (y, z) of the row's hits at
@@ -616,103 +760,13 @@ __device__ __forceinline__ void set_priority(uint32_t rows_left, uint32_t& level
   else __builtin_amdgcn_s_setprio(0);
 }
 
-// Chain fit and outward extension of tracklet i (seeded); false if the chain
-// fit fails, else the hand-off is written and key is its refit bucket.
-__device__ __forceinline__ bool up_one(const DevPtrs& d, const KfConst& k, const RowK* lrows, uint32_t i,
-                                       uint32_t& key, uint32_t& steps, uint32_t& prio) {
-  const uint32_t R = d.R, T = d.tcap;
-  const uint32_t sr0 = d.start_sr[i];
-  const uint32_t sec = sr0 / R, srb = sec * R, r0 = sr0 - srb;
-  const SectorConst sc = d.secs[sec];
-  const uint32_t rl = (uint32_t)d.tk_info[2 * T + i];
-  int32_t* H = d.tk_rowhit + i;     // row r at H[r * T]
-  float2 ho = d.syz[d.start_pos[i]];   // the outermost hit so far
-  const float zref = ho.y;
-  Trk t;
-#pragma unroll
-  for (int q = 0; q < 5; ++q) t.p[q] = par_t(d.tk_param[(size_t)q * T + i]);
-  set_c0(t, k);
-  float chi2 = 0.0f, xprev = lrows[r0].x;
-  par_t pout[3] = {t.p[2], t.p[3], t.p[4]};
-  uint32_t rout = rl;
-  int miss = 0;
-  bool failed = false;
-  // chain fit and outward extension, one row per iteration; while a row is
-  // stepped, the chain hits' coordinates are loaded two rows ahead (their
-  // indices three) and the next row's grid word one row ahead
-  const int32_t hk1 = r0 + 1 <= rl ? H[(size_t)(r0 + 1) * T] : -1;
-  float2 hnx = hk1 >= 0 ? d.syz[hk1] : make_float2(0.0f, 0.0f);
-  int32_t hk2 = r0 + 2 <= rl ? H[(size_t)(r0 + 2) * T] : -1;
-  float2 hn2 = hk2 >= 0 ? d.syz[hk2] : make_float2(0.0f, 0.0f);
-  int32_t hk3 = r0 + 3 <= rl ? H[(size_t)(r0 + 3) * T] : -1;
-  uint2 mnx = r0 + 1 < R && r0 + 1 > rl ? d.row_meta[srb + r0 + 1] : make_uint2(0u, 0u);
-  for (uint32_t r = r0 + 1; r < R; ++r) {
-    // issue priority by the rows still ahead (outward, then about as many inward): a wave far from its
-    // end goes first, so fewer waves are left running alone at the end (-1.6% on the 32-orbit frame)
-    set_priority(2 * (R - __builtin_amdgcn_readfirstlane(r)), prio);
-    const bool chain = r <= rl;
-    const float2 hc = hnx;
-    const uint2 meta = mnx;
-    hnx = hn2;
-    hn2 = hk3 >= 0 ? d.syz[hk3] : make_float2(0.0f, 0.0f);
-    hk3 = r + 3 <= rl ? H[(size_t)(r + 3) * T] : -1;
-    if (r + 1 < R && r + 1 > rl) mnx = d.row_meta[srb + r + 1];
-    ++steps;
-    const RowK rk = lrows[r];
-    const bool pok = propagate<true>(t, rk.x - xprev, k);
-    xprev = rk.x;
-    if (chain && !pok) {
-      failed = true;
-      break;
-    }
-    if (!chain && (!pok || fabs_(t.p[0]) > rk.half_y + k.margin)) break;
-    int32_t h = 0;   // chain rows hold a hit
-    float2 hm = hc;
-    if (!chain) {
-      h = search_m(d, meta, rk, sc, t, k, zref, hm);
-      H[(size_t)r * T] = h;
-    }
-    if (h >= 0) {
-      update(t, hm.x, hm.y - zref, k, chi2);
-      if (r >= rl) {
-        pout[0] = t.p[2];
-        pout[1] = t.p[3];
-        pout[2] = t.p[4];
-        rout = r;
-        ho = hm;
-        miss = 0;
-      }
-    } else if (++miss > k.max_miss) {
-      break;
-    }
-  }
-  if (failed) {
-    d.tk_info[i] = -2;   // the chain fit failed: no tracklet
-    return false;
-  }
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(pout[q]);
-    put_word(d, kHoPout + 2 * q, i, (uint32_t)b);
-    put_word(d, kHoPout + 2 * q + 1, i, (uint32_t)(b >> 32));
-  }
-  put_word(d, kHoHit, i, (uint32_t)__float_as_int(ho.x));
-  put_word(d, kHoHit + 1, i, (uint32_t)__float_as_int(ho.y));
-  put_word(d, kHoRout, i, rout);
-  put_word(d, kHoR0, i, r0);
-  put_word(d, kHoZref, i, (uint32_t)__float_as_int(zref));
-  put_word(d, kHoSec, i, sec);
-  key = srb + rout;
-  return true;
-}
-
 // The order in which an XCD's waves (64 consecutive tracklets or bucket slots
 // each) are started: most row steps first, by the start row (k_up) or the
 // outermost row (k_down) of the wave's ends.  An XCD holds 512 of them (four
 // per SIMD), and those started last run on with its SIMDs emptying; in plain
 // order they are as long as any, and on the 32-orbit frame (970 per XCD) 2.5
 // (k_up) and 2.9 (k_down) waves per SIMD were resident on average.  Ordered,
-// k_up takes 911 us instead of 1155 and k_down 1257 instead of 1348.
+// k_up took 911 us instead of 1155 and k_down 1257 instead of 1348 (before their searches were shared by the wave).
 // Only the last kOrdered waves are ordered: earlier ones are never among those
 // that run on, and the ordered waves of many sectors run side by side, which
 // the L2 pays for.  k_down, which reads more of each sector, is left in plain
@@ -755,17 +809,117 @@ __global__ void __launch_bounds__(kOrderThreads) k_order(DevPtrs d) {
 }
 
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_up(DevPtrs d, KfConst k) {
-  __shared__ RowK lrows[kMaxRows];
+  extern __shared__ RowK lrows[];   // of the R rows
+  __shared__ WaveSearch ws;
+  // the state at each lane's outermost hit so far (in LDS rather than registers)
+  __shared__ par_t out_p[3][kThreads];
+  __shared__ float2 out_hit[kThreads];
+  __shared__ uint32_t out_row[kThreads];
+  const uint32_t lane = threadIdx.x;
   const uint32_t nt = min(d.hdr->n_starts, d.tcap);
   const XcdSched sch = xcd_sched(nt);
   if (sch.first >= sch.end) return;   // the grid is sized for the tracklet capacity
   load_rows(d, lrows);
+  const uint32_t R = d.R, T = d.tcap;
   uint32_t steps = 0, prio = 0;
   for (uint32_t vb = sch.first; vb < sch.end; vb += sch.stride) {
     const uint32_t i = d.k5_order[vb] * kThreads + threadIdx.x;
-    bool on = i < nt && d.tk_info[i] >= 0;
+    bool on = i < nt && d.tk_info[i] >= 0;   // the lane's tracklet is still stepped
+    const bool mine = on;
+    const uint32_t sr0 = on ? d.start_sr[i] : 0;
+    const uint32_t sec = sr0 / R, srb = sec * R, r0 = sr0 - srb;
+    const SectorConst sc = d.secs[sec];
+    const uint32_t rl = on ? (uint32_t)d.tk_info[2 * T + i] : 0;
+    int32_t* H = d.tk_rowhit + i;     // row r at H[r * T]
+    const float2 h0 = on ? d.syz[d.start_pos[i]] : make_float2(0.0f, 0.0f);
+    const float zref = h0.y;
+    Trk t;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) t.p[q] = on ? par_t(d.tk_param[(size_t)q * T + i]) : par_t(0);
+    set_c0(t, k);
+    float chi2 = 0.0f, xprev = lrows[r0].x;
+    auto save = [&](float2 h, uint32_t r) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) out_p[q][lane] = t.p[2 + q];
+      out_hit[lane] = h;
+      out_row[lane] = r;
+    };
+    save(h0, rl);
+    int miss = 0;
+    bool failed = false;
+    // chain fit and outward extension, one row per iteration; while a row is
+    // stepped, the chain hits' coordinates are loaded two rows ahead (their
+    // indices three) and the next row's grid word one row ahead
+    const int32_t hk1 = r0 + 1 <= rl ? H[(size_t)(r0 + 1) * T] : -1;
+    float2 hnx = hk1 >= 0 ? d.syz[hk1] : make_float2(0.0f, 0.0f);
+    int32_t hk2 = r0 + 2 <= rl ? H[(size_t)(r0 + 2) * T] : -1;
+    float2 hn2 = hk2 >= 0 ? d.syz[hk2] : make_float2(0.0f, 0.0f);
+    int32_t hk3 = r0 + 3 <= rl ? H[(size_t)(r0 + 3) * T] : -1;
+    uint2 mnx = on && r0 + 1 < R && r0 + 1 > rl ? d.row_meta[srb + r0 + 1] : make_uint2(0u, 0u);
+    uint32_t r = r0 + 1;
+    on = on && r < R;
+    // the whole wave steps until its last lane ends: all lanes take part in the search (those that have ended keep
+    // their last values)
+    float2 hm = make_float2(0.0f, 0.0f);
+    uint2 meta = make_uint2(0u, 0u);
+    RowK rk{};
+    while (__any(on)) {
+      bool want = false;
+      if (on) {
+        // issue priority by the rows still ahead (outward, then about as many inward): a wave far from its
+        // end goes first, so fewer waves are left running alone at the end (-1.6% on the 32-orbit frame)
+        set_priority(2 * (R - __builtin_amdgcn_readfirstlane(r)), prio);
+        const bool chain = r <= rl;
+        hm = hnx;
+        meta = mnx;
+        hnx = hn2;
+        hn2 = hk3 >= 0 ? d.syz[hk3] : make_float2(0.0f, 0.0f);
+        hk3 = r + 3 <= rl ? H[(size_t)(r + 3) * T] : -1;
+        if (r + 1 < R && r + 1 > rl) mnx = d.row_meta[srb + r + 1];
+        ++steps;
+        rk = lrows[r];
+        const bool pok = propagate<true>(t, rk.x - xprev, k);
+        xprev = rk.x;
+        failed = chain && !pok;
+        on = pok && (chain || !(fabs_(t.p[0]) > rk.half_y + k.margin));
+        want = on && !chain;
+      }
+      int32_t h = search_wave(d, ws, want, meta, rk, sc, t, k, zref, hm);
+      if (on) {
+        if (want) H[(size_t)r * T] = h;
+        else h = 0;   // chain rows hold a hit
+        if (h >= 0) {
+          update(t, hm.x, hm.y - zref, k, chi2);
+          if (r >= rl) {
+            save(hm, r);
+            miss = 0;
+          }
+        } else if (++miss > k.max_miss) {
+          on = false;
+        }
+        on = on && ++r < R;
+      }
+    }
     uint32_t key = 0;
-    if (on) on = up_one(d, k, lrows, i, key, steps, prio);
+    if (mine && failed) d.tk_info[i] = -2;   // the chain fit failed: no tracklet
+    on = mine && !failed;
+    if (on) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const unsigned long long b = (unsigned long long)__double_as_longlong(out_p[q][lane]);
+        put_word(d, kHoPout + 2 * q, i, (uint32_t)b);
+        put_word(d, kHoPout + 2 * q + 1, i, (uint32_t)(b >> 32));
+      }
+      const float2 ho = out_hit[lane];
+      const uint32_t rout = out_row[lane];
+      put_word(d, kHoHit, i, (uint32_t)__float_as_int(ho.x));
+      put_word(d, kHoHit + 1, i, (uint32_t)__float_as_int(ho.y));
+      put_word(d, kHoRout, i, rout);
+      put_word(d, kHoR0, i, r0);
+      put_word(d, kHoZref, i, (uint32_t)__float_as_int(zref));
+      put_word(d, kHoSec, i, sec);
+      key = srb + rout;
+    }
     (void)wave_claim(d.row_nstart, key, on);   // count the tracklet in its refit bucket
   }
   uint32_t sum = steps;
@@ -792,10 +946,12 @@ __global__ void __launch_bounds__(256) k_sort(DevPtrs d) {
 }
 
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_down(DevPtrs d, KfConst k) {
-  __shared__ RowK lrows[kMaxRows];
+  extern __shared__ RowK lrows[];   // of the R rows
   // the state at each lane's innermost hit so far, in the float32 it is stored
   // in (in LDS rather than registers: four waves per SIMD instead of three)
   __shared__ f32x4 snap_s[5][kThreads];
+  __shared__ uint32_t nh_s[kThreads], rin_s[kThreads];
+  __shared__ WaveSearch ws;
   const uint32_t lane = threadIdx.x;
   auto save = [&](const Trk& t) {
     const Snap v = snap_of(t);
@@ -814,8 +970,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
   uint32_t steps = 0, prio = 0;
   for (uint32_t vb = sch.first; vb < sch.end; vb += sch.stride) {
     const uint32_t j = (sorted ? d.k5_order[vb] : vb) * kThreads + threadIdx.x;
-    if (j >= nv || (!sorted && d.tk_info[j] < 0)) continue;
-    const uint32_t i = sorted ? d.k5_perm[j] : j;
+    const bool mine = j < nv && (sorted || d.tk_info[j] >= 0);
+    const uint32_t i = !mine ? 0 : sorted ? d.k5_perm[j] : j;
     Trk t;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -824,9 +980,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
       t.p[2 + q] = __longlong_as_double((long long)b);
     }
     const float hy = __int_as_float((int)get_word(d, kHoHit, i)), hz = __int_as_float((int)get_word(d, kHoHit + 1, i));
-    const uint32_t rout = get_word(d, kHoRout, i), r0 = get_word(d, kHoR0, i);
+    const uint32_t rout = mine ? get_word(d, kHoRout, i) : 0, r0 = mine ? get_word(d, kHoR0, i) : 0;
     const float zref = __int_as_float((int)get_word(d, kHoZref, i));
-    const uint32_t sec = get_word(d, kHoSec, i), srb = sec * R;
+    const uint32_t sec = mine ? get_word(d, kHoSec, i) : 0, srb = sec * R;
     const SectorConst sc = d.secs[sec];
     int32_t* H = d.tk_rowhit + i;     // row r at H[r * T]
     // inward refit from the outermost hit, fresh covariance
@@ -834,9 +990,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     t.p[1] = hz - zref;
     set_c0(t, k);
     float chi2 = 0.0f;
-    int nh = 1;
+    nh_s[lane] = 1;
     save(t);
-    uint32_t rin = rout;
+    rin_s[lane] = rout;
     float xprev = lrows[rout].x;
     int miss = 0;
     // the outward pass's row -> hit entries are loaded three rows ahead and
@@ -846,39 +1002,54 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     float2 vA = hA >= 0 ? d.syz[hA] : make_float2(0.0f, 0.0f);
     float2 vB = hB >= 0 ? d.syz[hB] : make_float2(0.0f, 0.0f);
     uint2 mA = rout >= 1 ? d.row_meta[srb + rout - 1] : make_uint2(0u, 0u);
-    for (int r = (int)rout - 1; r >= 0; --r) {
-      set_priority(2 * (uint32_t)__builtin_amdgcn_readfirstlane(r), prio);
-      const int32_t hk = hA;
-      const float2 vk = vA;
-      const uint2 meta = mA;
-      hA = hB;
-      vA = vB;
-      hB = hC;
-      vB = hC >= 0 ? d.syz[hC] : make_float2(0.0f, 0.0f);
-      hC = known(r - 3);
-      if (r >= 1) mA = d.row_meta[srb + (uint32_t)r - 1];
-      const RowK rk = lrows[r];
-      ++steps;
-      if (!propagate<true>(t, rk.x - xprev, k)) break;
-      xprev = rk.x;
-      const bool below = (uint32_t)r < r0;
-      if (below && fabs_(t.p[0]) > rk.half_y + k.margin) break;
-      int32_t h = hk;
-      float2 hm = vk;
-      if (h < 0) h = search_m(d, meta, rk, sc, t, k, zref, hm);
-      // the row's entry changes only where the refit searched: below the start
-      // row (never written before) or in a gap the outward pass left
-      if (below || h != hk) H[(size_t)r * T] = h;
-      if (h >= 0) {
-        update(t, hm.x, hm.y - zref, k, chi2);
-        ++nh;
-        save(t);
-        rin = (uint32_t)r;
-        if (below) miss = 0;
-      } else if (below && ++miss > k.max_miss) {
-        break;
+    int r = (int)rout - 1;
+    bool on = mine && r >= 0;
+    float2 hm = make_float2(0.0f, 0.0f);
+    uint2 meta = make_uint2(0u, 0u);
+    RowK rk{};
+    int32_t h = -1;
+    while (__any(on)) {   // the whole wave, as in the outward pass
+      bool want = false, below = false;
+      if (on) {
+        set_priority(2 * (uint32_t)__builtin_amdgcn_readfirstlane(r), prio);
+        h = hA;
+        hm = vA;
+        meta = mA;
+        hA = hB;
+        vA = vB;
+        hB = hC;
+        vB = hC >= 0 ? d.syz[hC] : make_float2(0.0f, 0.0f);
+        hC = known(r - 3);
+        if (r >= 1) mA = d.row_meta[srb + (uint32_t)r - 1];
+        rk = lrows[r];
+        ++steps;
+        const bool pok = propagate<true>(t, rk.x - xprev, k);
+        xprev = rk.x;
+        below = (uint32_t)r < r0;
+        on = pok && !(below && fabs_(t.p[0]) > rk.half_y + k.margin);
+        want = on && h < 0;
+      }
+      const int32_t hs = search_wave(d, ws, want, meta, rk, sc, t, k, zref, hm);
+      if (on) {
+        if (want) h = hs;
+        // the row's entry changes only where the refit searched: below the start
+        // row (never written before) or in a gap the outward pass left
+        if (want && (below || h >= 0)) H[(size_t)r * T] = h;
+        if (h >= 0) {
+          update(t, hm.x, hm.y - zref, k, chi2);
+          __hip_atomic_fetch_add(&nh_s[lane], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+          save(t);
+          rin_s[lane] = (uint32_t)r;
+          if (below) miss = 0;
+        } else if (below && ++miss > k.max_miss) {
+          on = false;
+        }
+        on = on && --r >= 0;
       }
     }
+    if (!mine) continue;
+    const int nh = (int)nh_s[lane];
+    const uint32_t rin = rin_s[lane];
     Snap snap;
     const f32x4 w0 = snap_s[0][lane];
     snap.p[0] = w0.x;
@@ -1678,14 +1849,14 @@ void launch_tracklets(const DevPtrs& d, const KfConst& k, uint32_t max_row_hits,
   if (blocks > 16384) blocks = 16384;
   hipLaunchKernelGGL(k_seed, dim3(xcd_grid(blocks)), dim3(kThreads), 0, s, d, k);
   hipLaunchKernelGGL(k_order<false>, dim3(kXcds), dim3(kOrderThreads), 0, s, d);
-  hipLaunchKernelGGL(k_up, dim3(xcd_grid(blocks)), dim3(kThreads), 0, s, d, k);
+  hipLaunchKernelGGL(k_up, dim3(xcd_grid(blocks)), dim3(kThreads), d.R * sizeof(RowK), s, d, k);
   const uint32_t sort_blocks = std::min<uint32_t>((d.tcap + 255) / 256, 4096);
   if (d.k5_refit_order == 0) {
     launch_scan_u32(d.row_nstart, d.k5_off, d.SR, d.scan_blocks, s);
     hipLaunchKernelGGL(k_sort, dim3(sort_blocks), dim3(256), 0, s, d);
     hipLaunchKernelGGL(k_order<true>, dim3(kXcds), dim3(kOrderThreads), 0, s, d);
   }
-  hipLaunchKernelGGL(k_down, dim3(xcd_grid(blocks)), dim3(kThreads), 0, s, d, k);
+  hipLaunchKernelGGL(k_down, dim3(xcd_grid(blocks)), dim3(kThreads), d.R * sizeof(RowK), s, d, k);
   hipLaunchKernelGGL(k_guard, dim3(sort_blocks), dim3(256), 0, s, d);
 }
 

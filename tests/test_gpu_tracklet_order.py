@@ -68,3 +68,26 @@ def test_resident_sectors_change_nothing(kind, size):
         np.testing.assert_array_equal(getattr(got[0][0], k), getattr(got[1][0], k), err_msg=k)
     for a, b in zip(got[0][1:], got[1][1:]):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("overrides", [dict(), dict(gate_nsigma=40.0, win_cap=4.0), dict(gate_nsigma=40.0, win_cap=15.0),
+                                       dict(gate_nsigma=12.0, grid_hits_per_bin=1), dict(win_cap=0.02)])
+def test_wave_search_changes_nothing(overrides):
+    """Searches shared by the lanes of a wave (the lane-per-tracklet pipeline) against searches by the lanes of one
+    tracklet (row-synchronous): windows of no candidate, of one item, of several rounds of items, of two runs of bins and
+    of more.  The order of equal deviations is the same, so every result is, bit for bit."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2502_09138_amd.tracker import Tracker
+    ev = synth.single_sector(seed=21, n_tracks=500)
+    print("case: wave search", overrides, "N=", ev.n_clusters, flush=True)
+    tr = Tracker(default_config(**overrides), max_clusters=ev.n_clusters, max_sectors=1)
+    got = []
+    for schedule in (2, 1):
+        tr.set_knobs(schedule=schedule)
+        got.append(tr.track_event(ev, host=True))
+    tr.close()
+    assert got[0].n_tracklets == got[1].n_tracklets > 0
+    for k in FIELDS:
+        np.testing.assert_array_equal(getattr(got[0], k), getattr(got[1], k), err_msg=k)
