@@ -5,9 +5,9 @@
 // grids and refits inward with a fresh covariance, filling gaps and extending
 // below the chain.  Two schedules compute it: the row-synchronous kernel
 // (k_tracklets_rs, a wave sweeps the rows of one sector in lockstep with each
-// row staged in LDS; for frames whose rows fit the stage) and the
-// lane-per-tracklet pipeline (k_seed, k_up, k_sort, k_down, k_guard; any row
-// size).  The helix state p[5] and packed covariance C[15] are accumulated in
+// row staged in LDS where it fits; for frames whose waves are all resident, and
+// k_tracklets_res where whole sectors fit in LDS) and the lane-per-tracklet
+// pipeline (k_seed, k_up, k_sort, k_down, k_guard; larger frames).  The helix state p[5] and packed covariance C[15] are accumulated in
 // double registers (see par_t / cov_t); the per-step increments and the
 // Jacobian are float32.  The transport exploits the sparsity of the Jacobian
 // (6 non-trivial entries).
@@ -38,10 +38,6 @@ namespace tpc {
 namespace {
 
 constexpr int kThreads = 64;
-// Row-synchronous schedule: two lanes per tracklet (the pair splits the
-// candidate search and runs the rest of the step redundantly).
-constexpr int kPair = 2;
-constexpr int kTrkPerWave = kThreads / kPair;
 
 __device__ __forceinline__ int tri(int i, int j) { return i * (i + 1) / 2 + j; }   // i >= j
 
@@ -235,7 +231,7 @@ __device__ __forceinline__ void set_c0(Trk& t, const KfConst& k) {
 // hits between them are outside the window and fail its test, and a lane
 // whose window straddles two lines does not cost its wave a second group.
 constexpr int kGroup = 6;   // measured on the 32-orbit frame: 4 -> 6 is -3.7% in K5, 8 and above slower
-constexpr int kGroupLds = 4;   // candidates per group of the LDS search
+constexpr int kGroupLds = 4;   // most candidates that a lane of the LDS searches reads together
 constexpr int kRunBins = 3;    // z-lines of at most this many bins are searched as one run
 
 // two consecutive hits with one 16-byte load (hits are 8-byte aligned)
@@ -339,7 +335,23 @@ __device__ __forceinline__ uint32_t dpp_scan(uint32_t v, Op op) {
   return v;
 }
 
-__device__ __forceinline__ int32_t search_wave(const DevPtrs& d, WaveSearch& l, bool want, uint2 meta, const RowK& rk,
+// where the hits and bin starts are read: the frame's arrays, or a row staged in LDS (hits from position first, bins from
+// the row's first)
+struct InFrame {
+  const float2* yz;
+  const uint32_t* bs;
+  __device__ __forceinline__ uint32_t start(uint32_t b) const { return bs[b]; }
+  __device__ __forceinline__ const float2* at(uint32_t q) const { return yz + q; }
+};
+struct InStage {
+  const float2* yz;
+  const uint32_t* bs;
+  uint32_t first, bins;
+  __device__ __forceinline__ uint32_t start(uint32_t b) const { return bs[b - bins]; }
+  __device__ __forceinline__ const float2* at(uint32_t q) const { return yz + (q - first); }
+};
+template <class Row>
+__device__ __forceinline__ int32_t search_wave(const DevPtrs& d, const Row& row, WaveSearch& l, bool want, uint2 meta, const RowK& rk,
                                                const SectorConst& sc, const Trk& t, const KfConst& k, float zref,
                                                float2& hv) {
   if (!__any(want)) return -1;
@@ -368,11 +380,11 @@ __device__ __forceinline__ int32_t search_wave(const DevPtrs& d, WaveSearch& l, 
   // up to two runs per lane: [q0, h0) and [q1, h1)
   uint32_t q0 = 0, h0 = 0, q1 = 0, h1 = 0;
   if (want && !far) {
-    q0 = d.bin_start[b0];
-    h0 = d.bin_start[b1 + 1];
+    q0 = row.start(b0);
+    h0 = row.start(b1 + 1);
     if (b1 < e) {
-      q1 = d.bin_start[b0 + ny];
-      h1 = d.bin_start[b1 + ny + 1];
+      q1 = row.start(b0 + ny);
+      h1 = row.start(b1 + ny + 1);
     }
   }
   const uint32_t n0 = (h0 - q0 + kItem - 1) / kItem, n = n0 + (h1 - q1 + kItem - 1) / kItem;
@@ -406,7 +418,7 @@ __device__ __forceinline__ int32_t search_wave(const DevPtrs& d, WaveSearch& l, 
     float2 bh = make_float2(0.0f, 0.0f);
     if (slot < total) {
       float2 h[kItem];
-      const f32x4_at8* src = reinterpret_cast<const f32x4_at8*>(d.syz + q);
+      const f32x4_at8* src = reinterpret_cast<const f32x4_at8*>(row.at(q));
 #pragma unroll
       for (int j = 0; j < kItem / 2; ++j) {
         const f32x4 v = src[j];
@@ -443,21 +455,34 @@ __device__ __forceinline__ int32_t search_wave(const DevPtrs& d, WaveSearch& l, 
   return (int32_t)(uint32_t)best;
 }
 
+// Value of another lane of the kL lanes of a tracklet: a DPP move inside rows of 16.
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp_min(uint32_t v) {
+  return min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, kCtrl, 0xF, 0xF, false));
+}
+template <int kL>
+__device__ __forceinline__ uint32_t group_min(uint32_t v) {
+  if (kL >= 2) v = dpp_min<0xB1>(v);    // quad_perm 1,0,3,2
+  if (kL >= 4) v = dpp_min<0x4E>(v);    // quad_perm 2,3,0,1
+  if (kL >= 8) v = dpp_min<0x141>(v);   // row_half_mirror
+  if (kL >= 16) v = dpp_min<0x140>(v);  // row_mirror
+  return v;
+}
+
 // The same search over a row staged in LDS: (y, z) of the row's hits at
 // yz[q - first] and its bin starts (global positions) in bs[].  It is run by the
-// two lanes of a pair that carry the same tracklet: on every z-line they take
-// alternate groups of kGroupLds candidates, walking the z-lines as one flat
-// sequence, and then exchange their best candidates (a DPP swap inside the
-// pair, no LDS round trip).  A group is read whole: its entries past the
-// z-line's end (at most kGroupLds - 1, inside the stage's slack) are masked out.
+// kL lanes that carry the same tracklet: on every pair of z-lines they take kU
+// candidates in turn, walking the two lines as one flat sequence, and then
+// exchange their best candidates (DPP moves inside the tracklet's lanes, no LDS
+// round trip).  A turn is read whole: its entries past the z-line's end (at
+// most kGroupLds - 1, inside the stage's slack) are masked out.
 // The result -- smallest deviation, ties to the smaller position -- is the same
 // as a single ascending scan.
-__device__ __forceinline__ int pair_swap(int v) {   // value of the other lane of the pair (quad_perm 1,0,3,2)
-  return __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false);
-}
+template <int kL>
 __device__ __forceinline__ int32_t search_lds(const float2* yz, const uint32_t* bs, uint32_t first, uint2 meta,
                                               const RowK& rk, const SectorConst& sc, const Trk& t, const KfConst& k,
-                                              float zref, uint32_t half) {
+                                              float zref, uint32_t sub) {
+  constexpr int kU = kL == 2 ? 4 : 2;
   const float sy2 = float(t.c[0] + k.vyd), sz2 = float(t.c[2] + k.vzd);
   const float wy = fminf(k.gate * fsqrt(sy2), k.cap), wz = fminf(k.gate * fsqrt(sz2), k.cap);
   const float isy = frcp(sy2), isz = frcp(sz2);
@@ -468,47 +493,42 @@ __device__ __forceinline__ int32_t search_lds(const float2* yz, const uint32_t* 
   const int iy1 = bin1((yp + wy) + kWinPad, rk.y_lo, rk.inv_wy, ny);
   const int iz0 = bin1((za - wz) - kWinPad, sc.z_lo, sc.inv_wz, nz);
   const int iz1 = bin1((za + wz) + kWinPad, sc.z_lo, sc.inv_wz, nz);
-  int32_t best = -1;
-  float bd = 0.0f;
+  uint32_t best = 0xFFFFFFFFu;
+  float bd = INFINITY;
   // z-lines are taken two at a time (a window almost never spans more): the
   // candidates of the pair of lines form one flat sequence -- line iz, then
-  // line iz + 1, so positions ascend -- and the two lanes of a pair take
-  // alternate groups of it
+  // line iz + 1, so positions ascend -- and the lanes of a tracklet take kU of
+  // it in turn
   for (int iz = iz0; iz <= iz1; iz += 2) {
     const int izb = iz + 1 <= iz1 ? iz + 1 : iz;
     const uint32_t lo0 = bs[iz * ny + iy0], hi0 = bs[iz * ny + iy1 + 1];
     const uint32_t lo1 = bs[izb * ny + iy0], hi1 = bs[izb * ny + iy1 + 1];
     const uint32_t n0 = hi0 - lo0, tot = n0 + (izb > iz ? hi1 - lo1 : 0u);
-    for (uint32_t g0 = half * kGroupLds; g0 < tot; g0 += kPair * kGroupLds) {
-      uint32_t pos[kGroupLds];
-      float2 h[kGroupLds];
+    for (uint32_t g0 = sub * kU; g0 < tot; g0 += kL * kU) {
+      uint32_t pos[kU];
+      float2 h[kU];
 #pragma unroll
-      for (int j = 0; j < kGroupLds; ++j) {
-        const uint32_t f = g0 + j;   // past the end: at most kGroupLds - 1 entries beyond a line, masked below
+      for (int j = 0; j < kU; ++j) {
+        const uint32_t f = g0 + j;   // past the end: at most kU - 1 entries beyond a line, masked below
         pos[j] = f < n0 ? lo0 + f : lo1 + (f - n0);
         h[j] = yz[pos[j] - first];
       }
 #pragma unroll
-      for (int j = 0; j < kGroupLds; ++j) {
+      for (int j = 0; j < kU; ++j) {
         const float dy = h[j].x - yp, dz = (h[j].y - zref) - zp;
         if (g0 + j < tot && fabsf(dy) <= wy && fabsf(dz) <= wz) {
-          const float dd = dy * dy * isy + dz * dz * isz;
-          if (best < 0 || dd < bd) {
-            best = (int32_t)pos[j];
+          const float dd = __builtin_fmaf(dy * dy, isy, (dz * dz) * isz);
+          if (dd < bd) {
+            best = pos[j];
             bd = dd;
           }
         }
       }
     }
   }
-  // the pair's two candidates: smaller deviation, ties to the smaller position
-  const int32_t ob = pair_swap(best);
-  const float od = __int_as_float(pair_swap(__float_as_int(bd)));
-  if (ob >= 0 && (best < 0 || od < bd || (od == bd && ob < best))) {
-    best = ob;
-    bd = od;
-  }
-  return best;
+  // the lanes' candidates: smallest deviation (not negative, so its bits order as it does), ties to the smaller position
+  const uint32_t mine = (uint32_t)__float_as_int(bd), least = group_min<kL>(mine);
+  return (int32_t)group_min<kL>(mine == least ? best : 0xFFFFFFFFu);
 }
 
 // Three-point seed; false on failure.
@@ -884,7 +904,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         on = pok && (chain || !(fabs_(t.p[0]) > rk.half_y + k.margin));
         want = on && !chain;
       }
-      int32_t h = search_wave(d, ws, want, meta, rk, sc, t, k, zref, hm);
+      int32_t h = search_wave(d, InFrame{d.syz, d.bin_start}, ws, want, meta, rk, sc, t, k, zref, hm);
       if (on) {
         if (want) H[(size_t)r * T] = h;
         else h = 0;   // chain rows hold a hit
@@ -1029,7 +1049,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         on = pok && !(below && fabs_(t.p[0]) > rk.half_y + k.margin);
         want = on && h < 0;
       }
-      const int32_t hs = search_wave(d, ws, want, meta, rk, sc, t, k, zref, hm);
+      const int32_t hs = search_wave(d, InFrame{d.syz, d.bin_start}, ws, want, meta, rk, sc, t, k, zref, hm);
       if (on) {
         if (want) h = hs;
         // the row's entry changes only where the refit searched: below the start
@@ -1088,12 +1108,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
 
 // ---------------------------------------------------------------------------
 // Row-synchronous schedule ("coalesced row-grid reads").  A wave takes up to
-// 32 tracklets of ONE sector, two lanes per tracklet: the pair splits each
-// candidate search and runs the rest of the step redundantly, which shortens
-// the wave's per-row instruction stream (the longest waves' instruction issue
-// bounds this kernel: a central event's waves are all resident, 2-3 per SIMD,
-// and the SIMD favours those with the most rows still to step through).  After
-// each pair has walked its chain and built its seed, the wave sweeps the rows
+// 64 / kL tracklets of ONE sector, kL lanes per tracklet: they split each
+// candidate search and run the rest of the step redundantly (kL = 1: the whole
+// wave shares its searches, search_wave).  After each tracklet's lanes have
+// walked its chain and built its seed, the wave sweeps the rows
 // in lockstep -- outward, then inward --
 // and at every row stages that row's (y, z) and bin starts in LDS with one
 // coalesced load shared by all lanes; the loads for the next row are issued
@@ -1195,12 +1213,18 @@ __device__ __forceinline__ void commit_row(const Prefetch& pf, f32x4* yz4_s, u32
   for (int m = 0; m < kPreBs; ++m) bs4_s[lane + m * kThreads] = pf.bs[m];
 }
 
-// Three waves per SIMD (<= 168 VGPRs) keep every wave of a central event
-// resident at once.  The double-precision state then spills about 40 VGPRs
-// to scratch; measured on a central event this is faster than two waves per
-// SIMD without spills (0.86 against 1.09 ms).
-template <bool kAllFit>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) k_tracklets_rs(DevPtrs d, KfConst k) {
+// Bound: the longest wave's chain of some 300 row steps, each a stream of about
+// 500 vector instructions that one wave issues at one in 5 cycles (of 4400
+// cycles a step on a sector of 22k hits, 3200 are the step, 600 the next row's
+// loads and 260 the wait for them).  More lanes per tracklet shorten the step's
+// search, as long as the waves stay alone, or two together, on their SIMDs:
+// fewer lanes where there are more tracklets (row_lanes).  Registers: three
+// waves per SIMD at two lanes (a central event has 2400 waves; 24 values
+// spilled, and still faster than two waves per SIMD), two at one lane, any
+// number above, where nothing spills.
+template <bool kAllFit, int kL>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kL == 2 ? 3 : kL == 1 ? 2 : 1)))
+k_tracklets_rs(DevPtrs d, KfConst k) {
   __shared__ RowK lrows[kMaxRows];
   __shared__ f32x4 yz4_s[kPreYz * kThreads];   // the staged row: (y, z) pairs
   __shared__ u32x4 bs4_s[kPreBs * kThreads];   // and its bin starts
@@ -1208,6 +1232,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
   const uint32_t* bs_s = reinterpret_cast<const uint32_t*>(bs4_s);
   __shared__ uint32_t roff_s[kMaxRows + 1];   // the current sector's row offsets
   __shared__ uint2 meta_s[kMaxRows];          // and grid words
+  __shared__ WaveSearch ws;                    // kL = 1
   const uint32_t R = d.R, T = d.tcap, S = d.S;
   const uint32_t lane = threadIdx.x;
   const uint32_t W = d.wave_off[S];
@@ -1229,8 +1254,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
     }
     const uint32_t sec = lo, srb = sec * R;
     const uint32_t ts = min(d.row_start_off[srb], T), te = min(d.row_start_off[srb + R], T);
-    const uint32_t half = lane & 1u;   // both lanes of a pair compute the same tracklet and store identical values
-    const uint32_t i = ts + (v - d.wave_off[sec]) * kTrkPerWave + (lane >> 1);
+    const uint32_t sub = lane % kL;   // the lanes of a tracklet compute the same and store identical values
+    const uint32_t i = ts + (v - d.wave_off[sec]) * (kThreads / kL) + lane / kL;
     const SectorConst sc = d.secs[sec];
     int32_t* H = d.tk_rowhit + i;
     __syncthreads();   // the previous wave's last reads of the row table are done
@@ -1278,6 +1303,19 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
     int miss = 0;
     Stage st;
     Prefetch pf;
+    // the staged row's search: one lane's, or the wave's (called converged, for the lanes that want one)
+    auto find = [&](uint32_t sr, float2& hm) {
+      if (!(kAllFit || st.fits)) return search(d, sr, st.rk, sc, t, k, zref, hm);
+      const int32_t h = search_lds<kL>(yz_s, bs_s + st.boff, st.first, st.meta, st.rk, sc, t, k, zref, sub);
+      if (h >= 0) hm = yz_s[(uint32_t)h - st.first];
+      return h;
+    };
+    auto find_all = [&](bool want, float2& hm) {
+      return kAllFit || st.fits
+                 ? search_wave(d, InStage{yz_s, bs_s + st.boff, st.first, st.meta.x}, ws, want, st.meta, st.rk, sc, t, k, zref, hm)
+                 : search_wave(d, InFrame{d.syz, d.bin_start}, ws, want, st.meta, st.rk, sc, t, k, zref, hm);
+    };
+    auto hit = [&](int32_t h) { return (kAllFit || st.fits) ? yz_s[(uint32_t)h - st.first] : d.syz[h]; };
     uint32_t r = __builtin_amdgcn_readfirstlane(wave_min(up ? r0 + 1 : R));   // wave-uniform from here on
     if (r < R) {
       prefetch_row<kAllFit>(d, lrows, roff_s, meta_s, r, pf);
@@ -1296,26 +1334,15 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
       if (r + 1 < R) prefetch_row<kAllFit>(d, lrows, roff_s, meta_s, r + 1, pf);
       const int32_t hchain = hnext;
       hnext = (up && r + 1 <= rl && r + 1 > r0) ? H[(size_t)(r + 1) * T] : -1;
-      if (up && r > r0) {
-        // flags instead of nested branches: a lane that stops here keeps
-        // nothing of this step (its state is not read again)
-        const RowK rk = st.rk;
-        const bool chain = r <= rl;
-        steps += chain ? 0u : 1u;
-        const bool pok = propagate<true>(t, rk.x - xprev, k);
-        xprev = rk.x;
-        failed = failed || (!pok && chain);
-        const bool go = pok && (chain || fabs_(t.p[0]) <= rk.half_y + k.margin);
-        up = go;
-        int32_t h = hchain;
-        if (go && !chain) {
-          float2 unused;
-          h = (kAllFit || st.fits) ? search_lds(yz_s, bs_s + st.boff, st.first, st.meta, rk, sc, t, k, zref, half)
-                                   : search(d, srb + r, rk, sc, t, k, zref, unused);
-          H[(size_t)r * T] = h;
-        }
+      // flags instead of nested branches: a lane that stops here keeps nothing of this step (its state is not read again)
+      const bool chain = r <= rl;
+      bool go = false;
+      int32_t h = hchain;
+      float2 hm;
+      auto finish = [&] {
+        if (go && !chain) H[(size_t)r * T] = h;
         if (go && h >= 0) {
-          const float2 hm = (kAllFit || st.fits) ? yz_s[(uint32_t)h - st.first] : d.syz[h];
+          if (chain) hm = hit(h);
           update(t, hm.x, hm.y - zref, k, chi2);
           if (r >= rl) {
 #pragma unroll
@@ -1327,6 +1354,24 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
         const bool missed = go && h < 0;
         miss += missed ? 1 : 0;
         up = up && !(missed && miss > k.max_miss);
+      };
+      if (up && r > r0) {
+        const RowK rk = st.rk;
+        steps += chain ? 0u : 1u;
+        const bool pok = propagate<true>(t, rk.x - xprev, k);
+        xprev = rk.x;
+        failed = failed || (!pok && chain);
+        go = pok && (chain || fabs_(t.p[0]) <= rk.half_y + k.margin);
+        up = go;
+        if constexpr (kL > 1) {
+          if (go && !chain) h = find(srb + r, hm);
+          finish();
+        }
+      }
+      if constexpr (kL == 1) {
+        const int32_t hs = find_all(go && !chain, hm);
+        if (go && !chain) h = hs;
+        if (go) finish();
       }
       __syncthreads();
       if (r + 1 < R) commit_row(pf, yz4_s, bs4_s, st);
@@ -1367,23 +1412,14 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
       if (rr > 0) prefetch_row<kAllFit>(d, lrows, roff_s, meta_s, (uint32_t)rr - 1, pf);
       const int32_t hrow = hnext;
       hnext = (down && rr - 1 >= (int32_t)r0 && rr - 1 < (int32_t)rout) ? H[(size_t)(rr - 1) * T] : -1;
-      if (down && rr < (int32_t)rout) {
-        const RowK rk = st.rk;   // flags instead of nested branches, as in the outward sweep
-        ++steps;
-        const bool pok = propagate<true>(t, rk.x - xprev, k);
-        xprev = rk.x;
-        const bool below = (uint32_t)rr < r0;
-        const bool go = pok && !(below && fabs_(t.p[0]) > rk.half_y + k.margin);
-        down = go;
-        int32_t h = below ? -1 : hrow;
-        if (go && h < 0) {
-          float2 unused;
-          h = (kAllFit || st.fits) ? search_lds(yz_s, bs_s + st.boff, st.first, st.meta, rk, sc, t, k, zref, half)
-                                   : search(d, srb + (uint32_t)rr, rk, sc, t, k, zref, unused);
-        }
+      const bool below = (uint32_t)rr < r0;
+      bool go = false;
+      int32_t h = below ? -1 : hrow;
+      float2 hm;
+      auto finish = [&] {
         if (go && (below || h != hrow)) H[(size_t)rr * T] = h;   // changed only where the refit searched
         if (go && h >= 0) {
-          const float2 hm = (kAllFit || st.fits) ? yz_s[(uint32_t)h - st.first] : d.syz[h];
+          if (!below && h == hrow) hm = hit(h);
           update(t, hm.x, hm.y - zref, k, chi2);
           ++nh;
           snap = snap_of(t);
@@ -1393,6 +1429,23 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
         const bool missed = go && below && h < 0;
         miss += missed ? 1 : 0;
         down = down && !(missed && miss > k.max_miss);
+      };
+      if (down && rr < (int32_t)rout) {   // flags, as in the outward sweep
+        const RowK rk = st.rk;
+        ++steps;
+        const bool pok = propagate<true>(t, rk.x - xprev, k);
+        xprev = rk.x;
+        go = pok && !(below && fabs_(t.p[0]) > rk.half_y + k.margin);
+        down = go;
+        if constexpr (kL > 1) {
+          if (go && h < 0) h = find(srb + (uint32_t)rr, hm);
+          finish();
+        }
+      }
+      if constexpr (kL == 1) {
+        const int32_t hs = find_all(go && h < 0, hm);
+        if (go && h < 0) h = hs;
+        if (go) finish();
       }
       __syncthreads();
       if (rr > 0) commit_row(pf, yz4_s, bs4_s, st);
@@ -1401,7 +1454,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
     }
     if (ok) {
       store_tracklet<true>(d, i, nh, rin, rout, r0, snap, chi2, zref);
-      if (half == 0) my_steps += steps;
+      if (sub == 0) my_steps += steps;
     }
   }
   if (my_steps) atomicAdd(&d.hdr->n_steps, my_steps);
@@ -1459,20 +1512,6 @@ struct RowEntry {
   f32x4 k;
   u32x4 i;
 };
-
-// Value of another lane of the kL lanes of a tracklet: a DPP move inside rows of 16.
-template <int kCtrl>
-__device__ __forceinline__ uint32_t dpp_min(uint32_t v) {
-  return min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, kCtrl, 0xF, 0xF, false));
-}
-template <int kL>
-__device__ __forceinline__ uint32_t group_min(uint32_t v) {
-  if (kL >= 2) v = dpp_min<0xB1>(v);    // quad_perm 1,0,3,2
-  if (kL >= 4) v = dpp_min<0x4E>(v);    // quad_perm 2,3,0,1
-  if (kL >= 8) v = dpp_min<0x141>(v);   // row_half_mirror
-  if (kL >= 16) v = dpp_min<0x140>(v);  // row_mirror
-  return v;
-}
 
 // The search of C5 in a resident row: the place of the candidate closest to
 // the prediction, -1 if none.  Rows of few hits are tested whole; otherwise the
@@ -1793,9 +1832,9 @@ k_tracklets_res(DevPtrs d, KfConst k, ResLds l, uint32_t parts) {
   else resident_sector<2>(d, k, l, res_s, sec, part, parts);
 }
 
-// Waves of the row-synchronous schedule: ceil(tracklets of sector s / 32) per
-// sector, prefix-summed (one block).
-__global__ void __launch_bounds__(1024) k_waves(DevPtrs d) {
+// Waves of the row-synchronous schedule: ceil(tracklets of sector s / per_wave)
+// per sector, prefix-summed (one block).
+__global__ void __launch_bounds__(1024) k_waves(DevPtrs d, uint32_t per_wave) {
   __shared__ uint32_t wsum[1024 / kWave];
   const uint32_t S = d.S, R = d.R, T = d.tcap;
   const uint32_t per = (S + blockDim.x - 1) / blockDim.x;
@@ -1803,14 +1842,14 @@ __global__ void __launch_bounds__(1024) k_waves(DevPtrs d) {
   uint32_t sum = 0;
   for (uint32_t s = s0; s < s1; ++s) {
     const uint32_t a = min(d.row_start_off[s * R], T), b = min(d.row_start_off[(s + 1) * R], T);
-    sum += (b - a + kTrkPerWave - 1) / kTrkPerWave;
+    sum += (b - a + per_wave - 1) / per_wave;
   }
   uint32_t total;
   uint32_t run = block_exclusive_scan<uint32_t>(sum, wsum, &total);
   for (uint32_t s = s0; s < s1; ++s) {
     d.wave_off[s] = run;
     const uint32_t a = min(d.row_start_off[s * R], T), b = min(d.row_start_off[(s + 1) * R], T);
-    run += (b - a + kTrkPerWave - 1) / kTrkPerWave;
+    run += (b - a + per_wave - 1) / per_wave;
   }
   if (threadIdx.x == 0) d.wave_off[S] = total;
 }
@@ -1822,9 +1861,23 @@ hipError_t init_tracklets() {
   return hipFuncSetAttribute((const void*)k_tracklets_res, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResLdsBytes);
 }
 
+// Frames of up to this many hits are swept row by row, larger ones go through the pipeline: at 12 hits a tracklet (12 to 20
+// were seen) the waves of one lane per tracklet are then all resident, two on a SIMD (2048 * 64 * 12).  us of a call, pipeline / row by row: 4 dense
+// sectors, 0.92M hits 1420 / 1230; 40 chunks of up to 200k, 1.45M 1380 / 1260; with more
+// waves than are resident, 8 dense sectors, 1.86M 1690 / 2090; 9 heavy-ion orbits, 2.9M 1268 / 1530.
+constexpr uint32_t kRowSyncHits = 2048u * kWave * 12;
+// Lanes per tracklet, by the frame's hits (us at 8 / 4 / 2 / 1 lanes): 22k 607 / 629 / 700 / 828; 144k 636 / 622 / 672 / 774;
+// 324k 1041 / 719 / 714 / 829; 646k 1484 / 1093 / 812 / 907; 1.28M 2470 / 1615 / 968 / 981.  Two lanes only where all rows
+// are staged: their searches of a larger row are in global memory, each lane for itself (921k, rows of 1600: 1398 at two
+// lanes, 1229 at one).
+inline uint32_t row_lanes(uint32_t hits, bool staged) {
+  return hits <= (1u << 17) ? 8 : hits <= (1u << 18) ? 4 : staged && hits <= kRowSyncHits ? 2 : 1;
+}
+
 void launch_tracklets(const DevPtrs& d, const KfConst& k, uint32_t max_row_hits, hipStream_t s) {
   if (d.tcap == 0) return;
-  const bool rowsync = d.k5_mode == 2 || (d.k5_mode == 0 && max_row_hits <= (uint32_t)kStageHits);
+  const bool staged = max_row_hits <= (uint32_t)kStageHits;   // every row: the kernel carries no search in global memory
+  const bool rowsync = d.k5_mode == 2 || (d.k5_mode == 0 && d.N <= kRowSyncHits);
   // Resident sectors while their workgroups run side by side (three on a CU at most, by registers; about a tracklet per 16
   // hits): 60 chunks of up to 13k hits run 7% faster than row by row, 500 of up to 3k as fast, and 400 of up to 13k, one
   // workgroup on a CU at a time, 2.3 times as long.
@@ -1836,13 +1889,15 @@ void launch_tracklets(const DevPtrs& d, const KfConst& k, uint32_t max_row_hits,
     return;
   }
   if (rowsync) {
-    hipLaunchKernelGGL(k_waves, dim3(1), dim3(1024), 0, s, d);
-    uint32_t blocks = (d.tcap + kTrkPerWave - 1) / kTrkPerWave + d.S;
+    const uint32_t lanes = row_lanes(d.N, staged), per_wave = kThreads / lanes;
+    hipLaunchKernelGGL(k_waves, dim3(1), dim3(1024), 0, s, d, per_wave);
+    uint32_t blocks = (d.tcap + per_wave - 1) / per_wave + d.S;
     if (blocks > 16384) blocks = 16384;
-    if (max_row_hits <= (uint32_t)kStageHits)   // every row is staged: the kernel carries no global-memory search
-      hipLaunchKernelGGL(k_tracklets_rs<true>, dim3(xcd_grid(blocks)), dim3(kThreads), 0, s, d, k);
-    else
-      hipLaunchKernelGGL(k_tracklets_rs<false>, dim3(xcd_grid(blocks)), dim3(kThreads), 0, s, d, k);
+    auto kern = lanes == 8   ? (staged ? k_tracklets_rs<true, 8> : k_tracklets_rs<false, 8>)
+                : lanes == 4 ? (staged ? k_tracklets_rs<true, 4> : k_tracklets_rs<false, 4>)
+                : lanes == 2 ? k_tracklets_rs<true, 2>
+                             : k_tracklets_rs<false, 1>;
+    hipLaunchKernelGGL(kern, dim3(xcd_grid(blocks)), dim3(kThreads), 0, s, d, k);
     return;
   }
   uint32_t blocks = (d.tcap + kThreads - 1) / kThreads;

@@ -91,3 +91,29 @@ def test_wave_search_changes_nothing(overrides):
     assert got[0].n_tracklets == got[1].n_tracklets > 0
     for k in FIELDS:
         np.testing.assert_array_equal(getattr(got[0], k), getattr(got[1], k), err_msg=k)
+
+
+@pytest.mark.parametrize("sectors, primaries, n_min, n_max, staged",
+                         [(1, 220, 20000, 1 << 17, True), (1, 700, 20000, 1 << 17, False), (5, 240, 1 << 17, 1 << 18, True),
+                          (2, 700, 1 << 17, 1 << 18, False), (10, 240, 1 << 18, 1 << 20, True),
+                          (3, 900, 1 << 18, 1 << 20, False)])
+def test_row_by_row_lanes_change_nothing(sectors, primaries, n_min, n_max, staged):
+    """Row-by-row sweeps with 8, 4, 2 lanes and one lane a tracklet, rows staged or too large for it, against the
+    lane-per-tracklet pipeline, bit for bit."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2502_09138_amd.tracker import Tracker
+    ev = synth.central_event(seed=8, n_primaries=primaries * 36, sectors=range(sectors))
+    widest = int(np.diff(ev.row_offsets.astype(np.int64)).max())
+    print("case: row by row", sectors, primaries, "N=", ev.n_clusters, "widest row", widest, flush=True)
+    assert n_min < ev.n_clusters <= n_max and (widest <= 320) == staged
+    tr = Tracker(default_config(), max_clusters=ev.n_clusters, max_sectors=ev.n_sectors)
+    got = []
+    for schedule in (0, 1):
+        tr.set_knobs(schedule=schedule)
+        got.append(tr.track_event(ev, host=True))
+    tr.close()
+    assert got[0].n_tracklets == got[1].n_tracklets > 0
+    for k in FIELDS:
+        np.testing.assert_array_equal(getattr(got[0], k), getattr(got[1], k), err_msg=k)
