@@ -53,7 +53,7 @@ struct ResultHeader {
   uint64_t n_track_clusters;
   uint64_t n_steps;        // row steps taken by all tracklet lanes (C5 work measure)
   uint32_t link_retries;   // K2 tiles left to the large stage
-  uint32_t pad0;
+  uint32_t pipe_starts;    // K5: tracklets left to the pipeline where the device chose the schedule
   uint32_t codec_escaped;  // clusters the last C10 encoding stored raw
   uint32_t codec_unassigned;  // clusters on no track in the last C10 encoding
 };
@@ -130,6 +130,7 @@ struct DevPtrs {
   uint32_t tcap;
   uint32_t tile_cap;         // LDS words of one selector tile (max hits in a sector's row block)
   uint32_t max_sector_hits;  // hits of the largest sector
+  const uint32_t* pipe_n;    // K5: number of tracklets of the pipeline (of all of them, or hdr->pipe_starts)
   uint32_t res_blocks;       // K5: workgroups of 128 tracklets over all sectors, at a tracklet per 16 hits
   uint32_t n_link_tiles;     // K2 tiles of this request
   uint32_t n_packs;          // K1 row packs of this request

@@ -39,6 +39,9 @@ namespace {
 
 constexpr int kThreads = 64;
 
+// tracklets of the lane-per-tracklet pipeline: all, or none where the device has left them to the row-by-row sweeps
+__device__ __forceinline__ uint32_t pipe_n(const DevPtrs& d) { return min(*d.pipe_n, d.tcap); }
+
 __device__ __forceinline__ int tri(int i, int j) { return i * (i + 1) / 2 + j; }   // i >= j
 
 // Arithmetic types of the Kalman state p and of its covariance C.  Both are
@@ -634,7 +637,7 @@ __device__ __forceinline__ void store_tracklet(const DevPtrs& d, uint32_t i, int
 enum : int { kRecInfo = 0, kRecParam = 4, kRecCov = 9, kRecChi2 = 24, kRecWords = 25 };
 
 __global__ void __launch_bounds__(256) k_guard(DevPtrs d) {
-  const uint32_t nt = min(d.hdr->n_starts, d.tcap), T = d.tcap;
+  const uint32_t nt = pipe_n(d), T = d.tcap;
   const bool staged = d.k5_refit_order == 0;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nt; i += gridDim.x * blockDim.x) {
     if (staged) {
@@ -700,7 +703,7 @@ __global__ void __launch_bounds__(256) k_guard(DevPtrs d) {
 // grids of a few sectors only, which stay resident in that XCD's L2.
 __global__ void __launch_bounds__(kThreads) k_seed(DevPtrs d, KfConst k) {
   __shared__ float lx[kMaxRows];
-  const uint32_t nt = min(d.hdr->n_starts, d.tcap);
+  const uint32_t nt = pipe_n(d);
   const uint32_t R = d.R, T = d.tcap;
   // the bucket counts of k_up start at zero (the C4 row counts are not used after C4)
   for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < d.SR; q += gridDim.x * blockDim.x) d.row_nstart[q] = 0;
@@ -798,7 +801,7 @@ constexpr uint32_t kOrdered = kOrderThreads;
 template <bool kDown>
 __global__ void __launch_bounds__(kOrderThreads) k_order(DevPtrs d) {
   __shared__ uint32_t v[kOrderThreads];
-  const uint32_t n = kDown ? d.k5_off[d.SR] : min(d.hdr->n_starts, d.tcap), R = d.R;
+  const uint32_t n = kDown ? d.k5_off[d.SR] : pipe_n(d), R = d.R;
   const uint32_t need = (n + kThreads - 1) / kThreads, per = (need + kXcds - 1) / kXcds;
   const uint32_t first = min(need, blockIdx.x * per), b1 = min(need, first + per);
   const uint32_t b0 = kDown && b1 - first > kOrdered ? b1 : b1 - min(b1 - first, kOrdered), tid = threadIdx.x;
@@ -836,7 +839,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
   __shared__ float2 out_hit[kThreads];
   __shared__ uint32_t out_row[kThreads];
   const uint32_t lane = threadIdx.x;
-  const uint32_t nt = min(d.hdr->n_starts, d.tcap);
+  const uint32_t nt = pipe_n(d);
   const XcdSched sch = xcd_sched(nt);
   if (sch.first >= sch.end) return;   // the grid is sized for the tracklet capacity
   load_rows(d, lrows);
@@ -952,7 +955,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
 // holds the exclusive scan of the bucket counts (total at [SR]) and serves as
 // the buckets' fill cursors.
 __global__ void __launch_bounds__(256) k_sort(DevPtrs d) {
-  const uint32_t nt = min(d.hdr->n_starts, d.tcap), R = d.R;
+  const uint32_t nt = pipe_n(d), R = d.R;
   for (uint32_t b = blockIdx.x * blockDim.x; b < nt; b += gridDim.x * blockDim.x) {   // wave-uniform bounds
     const uint32_t i = b + threadIdx.x;
     const bool on = i < nt && d.tk_info[i] >= 0;
@@ -982,7 +985,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
   // bucket order: the refit tracklets (the scan total; the scatter moves only
   // [0, SR)); tracklet order: every tracklet, those without a hand-off skipped
   const bool sorted = d.k5_refit_order == 0;
-  const uint32_t nv = sorted ? d.k5_off[d.SR] : min(d.hdr->n_starts, d.tcap);
+  const uint32_t nv = sorted ? d.k5_off[d.SR] : pipe_n(d);
   const uint32_t R = d.R, T = d.tcap;
   const XcdSched sch = xcd_sched(nv);
   if (sch.first >= sch.end) return;   // the grid is sized for the tracklet capacity
@@ -1833,8 +1836,9 @@ k_tracklets_res(DevPtrs d, KfConst k, ResLds l, uint32_t parts) {
 }
 
 // Waves of the row-synchronous schedule: ceil(tracklets of sector s / per_wave)
-// per sector, prefix-summed (one block).
-__global__ void __launch_bounds__(1024) k_waves(DevPtrs d, uint32_t per_wave) {
+// per sector, prefix-summed (one block).  More than most of them: none, and the
+// tracklets are left to the pipeline.
+__global__ void __launch_bounds__(1024) k_waves(DevPtrs d, uint32_t per_wave, uint32_t most) {
   __shared__ uint32_t wsum[1024 / kWave];
   const uint32_t S = d.S, R = d.R, T = d.tcap;
   const uint32_t per = (S + blockDim.x - 1) / blockDim.x;
@@ -1851,7 +1855,10 @@ __global__ void __launch_bounds__(1024) k_waves(DevPtrs d, uint32_t per_wave) {
     const uint32_t a = min(d.row_start_off[s * R], T), b = min(d.row_start_off[(s + 1) * R], T);
     run += (b - a + per_wave - 1) / per_wave;
   }
-  if (threadIdx.x == 0) d.wave_off[S] = total;
+  if (threadIdx.x == 0) {
+    d.wave_off[S] = total > most ? 0 : total;
+    d.hdr->pipe_starts = total > most ? d.hdr->n_starts : 0;
+  }
 }
 
 }  // namespace
@@ -1861,11 +1868,15 @@ hipError_t init_tracklets() {
   return hipFuncSetAttribute((const void*)k_tracklets_res, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResLdsBytes);
 }
 
-// Frames of up to this many hits are swept row by row, larger ones go through the pipeline: at 12 hits a tracklet (12 to 20
-// were seen) the waves of one lane per tracklet are then all resident, two on a SIMD (2048 * 64 * 12).  us of a call, pipeline / row by row: 4 dense
-// sectors, 0.92M hits 1420 / 1230; 40 chunks of up to 200k, 1.45M 1380 / 1260; with more
-// waves than are resident, 8 dense sectors, 1.86M 1690 / 2090; 9 heavy-ion orbits, 2.9M 1268 / 1530.
-constexpr uint32_t kRowSyncHits = 2048u * kWave * 12;
+// Frames of up to kRowSyncHits hits are swept row by row: at 12 hits a tracklet (12 to 24 were seen) the waves of one lane
+// per tracklet are all resident, two on a SIMD.  Up to kRowSyncMaybe they may be, and the device decides on the number of
+// tracklets: both schedules are launched, and one finds nothing to do (8 launches, 45 us, or 2 launches, 8 us).  Larger
+// frames go through the pipeline.  us of a call, pipeline / row by row: 4 dense sectors, 0.92M hits 1420 / 1230; 40 chunks
+// of up to 200k, 1.45M 1380 / 1260; 8 heavy-ion orbits, 2.6M, 2008 waves 1228 / 1083 (1130 here); with more waves than are resident, 8
+// dense sectors, 1.86M 1690 / 2090; 9 heavy-ion orbits, 2.9M 1268 / 1530.
+constexpr uint32_t kResidentWaves = 2048;
+constexpr uint32_t kRowSyncHits = kResidentWaves * kWave * 12;
+constexpr uint32_t kRowSyncMaybe = kResidentWaves * kWave * 24;
 // Lanes per tracklet, by the frame's hits (us at 8 / 4 / 2 / 1 lanes): 22k 607 / 629 / 700 / 828; 144k 636 / 622 / 672 / 774;
 // 324k 1041 / 719 / 714 / 829; 646k 1484 / 1093 / 812 / 907; 1.28M 2470 / 1615 / 968 / 981.  Two lanes only where all rows
 // are staged: their searches of a larger row are in global memory, each lane for itself (921k, rows of 1600: 1398 at two
@@ -1874,10 +1885,13 @@ inline uint32_t row_lanes(uint32_t hits, bool staged) {
   return hits <= (1u << 17) ? 8 : hits <= (1u << 18) ? 4 : staged && hits <= kRowSyncHits ? 2 : 1;
 }
 
-void launch_tracklets(const DevPtrs& d, const KfConst& k, uint32_t max_row_hits, hipStream_t s) {
-  if (d.tcap == 0) return;
+void launch_tracklets(const DevPtrs& frame, const KfConst& k, uint32_t max_row_hits, hipStream_t s) {
+  if (frame.tcap == 0) return;
+  DevPtrs d = frame;
   const bool staged = max_row_hits <= (uint32_t)kStageHits;   // every row: the kernel carries no search in global memory
-  const bool rowsync = d.k5_mode == 2 || (d.k5_mode == 0 && d.N <= kRowSyncHits);
+  const bool maybe = d.k5_mode == 0 && d.N > kRowSyncHits && d.N <= kRowSyncMaybe;
+  const bool rowsync = maybe || d.k5_mode == 2 || (d.k5_mode == 0 && d.N <= kRowSyncHits);
+  d.pipe_n = maybe ? &d.hdr->pipe_starts : &d.hdr->n_starts;
   // Resident sectors while their workgroups run side by side (three on a CU at most, by registers; about a tracklet per 16
   // hits): 60 chunks of up to 13k hits run 7% faster than row by row, 500 of up to 3k as fast, and 400 of up to 13k, one
   // workgroup on a CU at a time, 2.3 times as long.
@@ -1890,7 +1904,7 @@ void launch_tracklets(const DevPtrs& d, const KfConst& k, uint32_t max_row_hits,
   }
   if (rowsync) {
     const uint32_t lanes = row_lanes(d.N, staged), per_wave = kThreads / lanes;
-    hipLaunchKernelGGL(k_waves, dim3(1), dim3(1024), 0, s, d, per_wave);
+    hipLaunchKernelGGL(k_waves, dim3(1), dim3(1024), 0, s, d, per_wave, maybe ? kResidentWaves : ~0u);
     uint32_t blocks = (d.tcap + per_wave - 1) / per_wave + d.S;
     if (blocks > 16384) blocks = 16384;
     auto kern = lanes == 8   ? (staged ? k_tracklets_rs<true, 8> : k_tracklets_rs<false, 8>)
@@ -1898,7 +1912,7 @@ void launch_tracklets(const DevPtrs& d, const KfConst& k, uint32_t max_row_hits,
                 : lanes == 2 ? k_tracklets_rs<true, 2>
                              : k_tracklets_rs<false, 1>;
     hipLaunchKernelGGL(kern, dim3(xcd_grid(blocks)), dim3(kThreads), 0, s, d, k);
-    return;
+    if (!maybe) return;
   }
   uint32_t blocks = (d.tcap + kThreads - 1) / kThreads;
   if (blocks > 16384) blocks = 16384;

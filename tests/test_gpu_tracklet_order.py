@@ -96,10 +96,11 @@ def test_wave_search_changes_nothing(overrides):
 @pytest.mark.parametrize("sectors, primaries, n_min, n_max, staged",
                          [(1, 220, 20000, 1 << 17, True), (1, 700, 20000, 1 << 17, False), (5, 240, 1 << 17, 1 << 18, True),
                           (2, 700, 1 << 17, 1 << 18, False), (10, 240, 1 << 18, 1 << 20, True),
-                          (3, 900, 1 << 18, 1 << 20, False)])
+                          (3, 900, 1 << 18, 1 << 20, False), (36, 330, 3 << 19, 3 << 20, False),
+                          (8, 1600, 3 << 19, 3 << 20, False)])
 def test_row_by_row_lanes_change_nothing(sectors, primaries, n_min, n_max, staged):
-    """Row-by-row sweeps with 8, 4, 2 lanes and one lane a tracklet, rows staged or too large for it, against the
-    lane-per-tracklet pipeline, bit for bit."""
+    """Row-by-row sweeps with 8, 4, 2 lanes and one lane a tracklet, rows staged or too large for it, and the
+    schedule left to the device (few enough tracklets, and too many), against the lane-per-tracklet pipeline, bit for bit."""
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
