@@ -19,8 +19,8 @@
 //                  into per-tile prefixes and packs (owned << 32) | accepted for
 //                  one 64-bit scan giving track index and cluster offset;
 //   k_records      writes the per-track records (canonical order = tracklet
-//                  order = ascending start position) and the track -> tracklet
-//                  list;
+//                  order = ascending start position) and, by track, what the
+//                  emit reads of it;
 //   k_emit_tiles   walks the sector's tracks (not all its tracklets) and writes
 //                  the owned cluster ids of each at offset + prefix, row by row
 //                  (ascending row order);
@@ -176,6 +176,15 @@ __global__ void __launch_bounds__(kThreads) k_accept(DevPtrs d, KfConst k, uint3
   }
 }
 
+// What the tiled emit needs of a track, by track: written by k_records into the tracklet pipeline's records, which are not
+// used after C5.  Every tile of a sector reads them, in order; gathered from five tracklet arrays, of which a track is one
+// entry in four, they cost the emit a seventh of its time (C6/C7 on the 32-orbit frame 368 -> 345 us, 512 chunks 870 -> 813).
+struct alignas(16) EmitRec {
+  uint32_t tracklet, key, clusters;   // clusters: the track's place in the output
+  uint32_t rows;                      // first row | last row << 16; first > last: not written (over capacity)
+};
+__device__ __forceinline__ EmitRec* emit_recs(const DevPtrs& d) { return reinterpret_cast<EmitRec*>(d.k5_rec); }
+
 template <int kT>
 __global__ void __launch_bounds__(kT) k_emit_tiles(DevPtrs d, KfConst k, uint32_t tile_rows, uint32_t n_tiles) {
   extern __shared__ uint32_t wt[];
@@ -192,23 +201,20 @@ __global__ void __launch_bounds__(kT) k_emit_tiles(DevPtrs d, KfConst k, uint32_
   // kBatch tracks per thread at a time, each stage's loads issued together
   for (uint32_t vb = v0 + threadIdx.x; vb < v1; vb += kBatch * kT) {
     uint32_t i[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) i[u] = vb + u * kT < v1 ? d.acc_list[vb + u * kT] : 0u;
     bool go[kBatch];
     uint32_t o[kBatch], key[kBatch];
     int32_t lo[kBatch], hi[kBatch];
+    EmitRec rec[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) rec[u] = vb + u * kT < v1 ? emit_recs(d)[vb + u * kT] : EmitRec{0, 0, 0, 1};
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const bool in = vb + u * kT < v1;
-      const unsigned long long pk = in ? d.tk_pack[i[u]] : 0ull;
-      const unsigned long long co = in ? d.tk_scan[i[u]] >> 32 : 0ull;
-      const int32_t nh = in ? d.tk_info[i[u]] : 0;
-      lo[u] = max((int32_t)tl.ra, in ? d.tk_info[T + i[u]] : 0);
-      hi[u] = min((int32_t)tl.rb - 1, in ? d.tk_info[2 * T + i[u]] : -1);
-      const uint32_t pre = in ? d.own_part[(size_t)tt * T + i[u]] : 0u;
-      go[u] = in && co + (pk >> 32) <= d.max_track_clusters && lo[u] <= hi[u];   // capacity: flagged by finish()
-      key[u] = key32((uint32_t)nh, i[u]);
-      o[u] = (uint32_t)co + pre;
+      i[u] = rec[u].tracklet;
+      key[u] = rec[u].key;
+      lo[u] = max((int32_t)tl.ra, (int32_t)(rec[u].rows & 0xFFFFu));
+      hi[u] = min((int32_t)tl.rb - 1, (int32_t)(rec[u].rows >> 16));
+      go[u] = lo[u] <= hi[u];
+      o[u] = rec[u].clusters + (go[u] ? d.own_part[(size_t)tt * T + i[u]] : 0u);
     }
     int32_t h[kBatch][kTileRowsMax];
 #pragma unroll
@@ -270,13 +276,14 @@ __global__ void __launch_bounds__(kThreads) k_records(DevPtrs d, KfConst k, bool
     const uint32_t ti = (uint32_t)(pre & 0xFFFFFFFFull);
     const unsigned long long co = pre >> 32;
     if (ti >= d.max_tracks) continue;                          // flagged by finish()
-    d.acc_list[ti] = i;                                        // track -> tracklet, for the tiled emit
-    if (co + (pk >> 32) > d.max_track_clusters) continue;
-    const int32_t nh = d.tk_info[i];
+    const bool fits = co + (pk >> 32) <= d.max_track_clusters;
+    const int32_t nh = d.tk_info[i], rin = d.tk_info[T + i], rout = d.tk_info[2 * T + i];
+    emit_recs(d)[ti] = EmitRec{i, key32((uint32_t)nh, i), (uint32_t)co, fits ? (uint32_t)rin | (uint32_t)rout << 16 : 1u};
+    if (!fits) continue;
     d.out_sector[ti] = d.start_sr[i] / d.R;
     d.out_start[ti] = d.start_pos[i];
     d.out_first[ti] = (uint32_t)co;
-    d.out_xref[ti] = d.rows[d.tk_info[T + i]].x;
+    d.out_xref[ti] = d.rows[rin].x;
 #pragma unroll
     for (int q = 0; q < 5; ++q) d.out_param[(size_t)ti * 5 + q] = d.tk_param[(size_t)q * T + i];
 #pragma unroll

@@ -56,7 +56,7 @@ constexpr uint32_t kSelectGlobal = 0xFFFFFFFFu;  // TPC_KNOB_SELECT_TILE_ROWS = 
 struct Layout {   // byte offsets of every workspace buffer
   uint64_t row_off, rows, secs, pack_first, row_dims, row_meta, bin_start, syz, sid, up0, down0, up1, down1, sflag, row_nstart,
       row_start_off, start_pos, start_sr, wave_off, tile_off, tile_sr, tk_rowhit, tk_info, tk_param, tk_cov, tk_chi2, k5_off, k5_perm, k5_inv, k5_rec, W, own_part, tk_pack,
-      tk_scan, acc_list,
+      tk_scan,
       out_sector, out_start, out_first, out_clusters, out_xref, out_param, out_cov, out_chi2, out_ndf, scan_blocks,
       hdr, in_y, in_z, m_phys, m_nbr, m_sec_first, m_succ, m_pred_key, m_next, m_has_pred, m_head_flag, m_head_scan,
       m_chain_cl, m_cl_scan, m_heads, m_head_of, m_first, m_clusters, m_param, m_cov, m_chi2, m_ndf, m_nseg, total;
@@ -124,7 +124,6 @@ Layout layout_of(const Caps& k) {
   L.own_part = take((uint64_t)k.R * k.T);
   L.tk_pack = take(k.T * 8);
   L.tk_scan = take((k.T + 1) * 8);
-  L.acc_list = take((k.MT + 1) * 4);
   L.out_sector = take(k.MT * 4);
   L.out_start = take(k.MT * 4);
   L.out_first = take((k.MT + 1) * 4);
@@ -303,7 +302,6 @@ void carve(tpc_tracker* t) {
   d.tk_pack = (unsigned long long*)(w + lay.tk_pack);
   d.k5_order = (uint32_t*)d.tk_pack;
   d.tk_scan = (unsigned long long*)(w + lay.tk_scan);
-  d.acc_list = (uint32_t*)(w + lay.acc_list);
   d.out_sector = (uint32_t*)(w + lay.out_sector);
   d.out_start = (uint32_t*)(w + lay.out_start);
   d.out_first = (uint32_t*)(w + lay.out_first);
