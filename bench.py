@@ -50,14 +50,14 @@ PROFILE_SOURCES = (
 )
 PROFILES = {
     "time_frame": {
-        "digests": ("e6f5144456141a8ece92fb362dab16b7baf29c14", "c842c467a72239a1275ba70e0d941297d2d258a8",
-                    "0c2bdc7fab0f213bed5c4784cc480462ad908377", "b4b103e57db5db269528a9bdae40217f2bb52ff1",
-                    "9cd7cf284155efdc8f0dcaf15d9b2a7a4972b985"),
+        "digests": ("17173b93fe894ebef3414af21e83e25359411bfa", "9376327f84ab69314b3d89e2fbd807306ff31fa6",
+                    "b9c01736632ed5cde0730e9777a6b8663234cc85", "831c9a0cc463abecb232e02f8e38b3ee4492a863",
+                    "e7e0bd5e3bde6e628b9870c1e5f689130b3c0acd"),
         "knobs": {"schedule": 1, "select_tile_rows": 4, "refit_order": 0, "link_slots": 4, "link_group": -1,
                   "select_threads": 1024},
         # tracklets: k_seed + k_up + k_sort + k_down + k_guard; VALU of k_up and k_down (the rest is < 5%)
-        "traffic_bytes": {"tracklets": 5_473_990_000, "grid": 292_040_000, "neighbours": 182_370_000},
-        "valu_insts": {"tracklets": 960_531_614, "grid": 21_682_775, "neighbours": 247_349_791},
+        "traffic_bytes": {"tracklets": 4_716_400_000, "grid": 292_070_000, "neighbours": 182_230_000},
+        "valu_insts": {"tracklets": 868_535_923, "grid": 21_038_144, "neighbours": 156_074_340},
         "files": "profiles/time_frame_hbm_traffic.md, profiles/time_frame_sq_counters.md",
     },
 }
