@@ -216,6 +216,36 @@ class Tracks:
         return len(self.sector)
 
 
+class _HostMemory:
+    """An array of the library's pinned memory, by address (numpy's array interface)."""
+    __slots__ = ("__array_interface__",)
+
+    def __init__(self, address, count, dtype):
+        self.__array_interface__ = dict(data=(address, False), shape=(count,), typestr=dtype.str, version=3)
+
+
+# Arrays from this size on are copied by several threads: into fresh memory one thread takes 151 us for 2 MB and 857 for
+# 9.6 MB, eight take 44 and 218; at 0.8 MB they take the same.
+_THREADED_COPY_BYTES = 1 << 20
+
+
+def _host_array(ptr, count, dtype, copy):
+    """A view of count elements at ptr, or a numpy array of its own with their values.  The array interface makes no
+    ctypes array type, which costs 20 us for every new size."""
+    dtype = np.dtype(dtype)
+    if count == 0:
+        return np.zeros(0, dtype)
+    view = np.asarray(_HostMemory(C.cast(ptr, C.c_void_p).value, count, dtype))
+    if not copy:
+        return view
+    if view.nbytes < _THREADED_COPY_BYTES:
+        return view.copy()
+    import torch
+    out = np.empty(count, dtype)
+    torch.from_numpy(out.view(np.int32)).copy_(torch.from_numpy(view.view(np.int32)))   # all types here are 32-bit
+    return out
+
+
 class Tracker:
     """One tracker on one GPU; workspace and stream come from torch."""
 
@@ -315,9 +345,7 @@ class Tracker:
         n, nc = t.n_tracks, t.n_track_clusters
 
         def arr(ptr, count, dt):
-            if count == 0:
-                return np.zeros(0, dt)
-            return np.ctypeslib.as_array(ptr, shape=(count,)).astype(dt, copy=copy)
+            return _host_array(ptr, count, dt, copy)
 
         return Tracks(n_tracklets=t.n_tracklets, error_flags=t.error_flags,
                       sector=arr(t.track_sector, n, np.uint32), start=arr(t.track_start, n, np.uint32),
@@ -351,9 +379,7 @@ class Tracker:
         n, nc, ncl = m.n_tracks, m.n_chains, m.n_chain_clusters
 
         def arr(ptr, count, dt):
-            if count == 0:
-                return np.zeros(0, dt)
-            return np.ctypeslib.as_array(ptr, shape=(count,)).astype(dt, copy=True)
+            return _host_array(ptr, count, dt, True)
 
         return dict(next=arr(m.next, n, np.int32), head_of=arr(m.head_of, n, np.uint32),
                     heads=arr(m.heads, nc, np.uint32), nseg=arr(m.nseg, nc, np.int32),
