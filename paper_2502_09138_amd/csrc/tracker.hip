@@ -573,7 +573,7 @@ tpc_status tpc_tracker_bind_workspace(tpc_tracker* t, void* workspace, uint64_t 
 namespace {
 
 // The outputs of a request or of a merge to pinned host memory: array blockIdx.y, in 16-byte units (arrays start at 256 bytes on both
-// sides, and the units that they end in lie inside them there).  Bound: the host link.  One launch instead of nine copies:
+// sides, and the units that they end in lie inside them there).  Bound: the host link.  One launch instead of nine or ten copies:
 // a call on a pp frame of one orbit (0.4 MB) takes 553 instead of 590 us with the other launches saved here, one of 7 MB
 // 1331 instead of 1400, one of 13 MB 2018 instead of 2085; a merge of 8 orbits 1080 instead of 1170, of one 453 instead of 525.
 constexpr int kExportMax = 10;
