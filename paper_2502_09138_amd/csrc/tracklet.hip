@@ -1615,7 +1615,9 @@ __device__ __forceinline__ RowInfo row_info(const RowEntry& e) {
 
 // Chain, seed and both sweeps of tracklet i, kL lanes; returns its row steps on
 // the lane that writes.  col[r * kPer] is the hit in row r, as its place in the
-// row.
+// row: one lane of the tracklet writes it and all of them read it, so every
+// point between the two is ordered (no instruction: a wave's LDS accesses
+// complete in order).
 template <int kL, uint32_t kPer>
 __device__ __forceinline__ uint32_t sweep(const DevPtrs& d, const KfConst& k, const Resident& S, uint8_t* col, uint32_t sec,
                                           uint32_t i, uint32_t te) {
@@ -1626,6 +1628,7 @@ __device__ __forceinline__ uint32_t sweep(const DevPtrs& d, const KfConst& k, co
   uint32_t r0 = 0, rl = 0, n = 0;
   float zref = 0.0f, chi2 = 0.0f, xprev = 0.0f;
   Trk t;
+  wave_lds_order();   // the lanes' last reads of the previous tracklet's column
   if (ok) {
     r0 = d.start_sr[i] - sec * R;
     const uint32_t p0 = d.start_pos[i] - S.a0;
@@ -1655,6 +1658,7 @@ __device__ __forceinline__ uint32_t sweep(const DevPtrs& d, const KfConst& k, co
   par_t pout[3] = {t.p[2], t.p[3], t.p[4]};
   uint32_t rout = rl;
   int miss = 0;
+  wave_lds_order();   // the chain's rows of the column
   uint32_t r = uniform(wave_min(up ? r0 + 1 : R));
   RowEntry next = S.entry(r < R ? r : 0);
   uint32_t hnext = r < R ? col[r * kPer] : kNoHit;   // used only in chain rows
@@ -1691,6 +1695,7 @@ __device__ __forceinline__ uint32_t sweep(const DevPtrs& d, const KfConst& k, co
       miss += missed ? 1 : 0;
       up = up && !(missed && miss > k.max_miss);
     }
+    wave_lds_order();   // the row's column entry
   }
   if (failed) {
     if (writes) d.tk_info[i] = -2;
@@ -1746,6 +1751,7 @@ __device__ __forceinline__ uint32_t sweep(const DevPtrs& d, const KfConst& k, co
       miss += missed ? 1 : 0;
       down = down && !(missed && miss > k.max_miss);
     }
+    wave_lds_order();   // the row's column entry
   }
   if (!ok) return 0;
   int32_t* H = d.tk_rowhit + i;     // the column's rows that the selector reads
