@@ -378,8 +378,8 @@ typedef struct {
  * finite, > 0).  Runs on the tracker's stream and waits for it; *counts
  * receives the stream's sizes.  The stream arrays are sized by the caller from
  * the request's track counts (tpc_get_tracks) and the frame's cluster count.
- * Uses the request's workspace for flags (its C2 and C6 intermediates are
- * overwritten).  TPC_E_INVAL for an unknown request, bad quanta or NULL
+ * Uses the request's workspace for flags (none of the arrays that
+ * tpc_debug_copy returns).  TPC_E_INVAL for an unknown request, bad quanta or NULL
  * arrays; TPC_E_INPUT/TPC_E_CAPACITY if the request failed. */
 tpc_status tpc_encode_tracks(tpc_tracker* t, uint64_t request_id, float q_y, float q_z, const tpc_codec_stream* out,
                              tpc_codec_counts* counts);

@@ -167,10 +167,9 @@ __global__ void __launch_bounds__(kThreads) k_codec_models(CodecArgs a) {
   }
   __syncthreads();
   uint32_t c = 0;
-  for (uint32_t w = threadIdx.x; w < words; w += kThreads) {
-    a.un_bits[b + w] = bits[w];
-    c += (uint32_t)__popc(bits[w]);
-  }
+  for (uint32_t w = threadIdx.x; w < words; w += kThreads) c += (uint32_t)__popc(bits[w]);
+  for (uint32_t w = threadIdx.x; w < (n + 7) / 8; w += kThreads)
+    a.un_bits[b + w] = (uint8_t)(bits[w / 4] >> (8 * (w % 4)));
   uint32_t total;
   (void)block_exclusive_scan<uint32_t>(c, wsum, &total);
   if (threadIdx.x == 0) a.row_cnt[sr] = total;
@@ -178,14 +177,14 @@ __global__ void __launch_bounds__(kThreads) k_codec_models(CodecArgs a) {
 
 // The raw list of row sr, in input order.
 __device__ __forceinline__ void emit_row(const CodecArgs& a, uint32_t sr, uint32_t* wsum) {
-  const uint32_t b = a.row_off[sr], n = a.row_off[sr + 1] - b, words = (n + 31) / 32;
+  const uint32_t b = a.row_off[sr], n = a.row_off[sr + 1] - b, bytes = (n + 7) / 8;
   uint32_t base = a.row_pos[sr];
-  for (uint32_t w0 = 0; w0 < words; w0 += kThreads) {   // block-uniform chunks
+  for (uint32_t w0 = 0; w0 < bytes; w0 += kThreads) {   // block-uniform chunks
     const uint32_t w = w0 + threadIdx.x;
-    uint32_t v = w < words ? a.un_bits[b + w] : 0u, total;
+    uint32_t v = w < bytes ? a.un_bits[b + w] : 0u, total;
     uint32_t k = base + block_exclusive_scan<uint32_t>((uint32_t)__popc(v), wsum, &total);
     for (; v; v &= v - 1, ++k) {
-      const uint32_t i = b + w * 32 + (uint32_t)__ffs((int)v) - 1;
+      const uint32_t i = b + w * 8 + (uint32_t)__ffs((int)v) - 1;
       a.un_row[k] = (uint8_t)(sr % a.R);
       reinterpret_cast<float2*>(a.un_yz)[k] = make_float2(a.y[i], a.z[i]);
     }

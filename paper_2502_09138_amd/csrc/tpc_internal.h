@@ -201,7 +201,7 @@ struct CodecArgs {
   const uint32_t* sid;         // [N] input cluster per sorted position
   const unsigned long long* tk_pack;   // [tracklets] bit 0: accepted
   // workspace scratch
-  uint32_t* un_bits;           // [N] per row, from its first word: bit i = input cluster i of the row is on no track
+  uint8_t* un_bits;            // [N] per row, from its first byte: bit i = input cluster i of the row is on no track
   uint32_t* row_cnt;           // [SR] clusters on no track per (sector, row)
   uint32_t* row_pos;           // [SR + 1] exclusive scan of row_cnt
   uint32_t* n_escaped;

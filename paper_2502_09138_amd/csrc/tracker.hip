@@ -1038,9 +1038,9 @@ tpc_status tpc_encode_tracks(tpc_tracker* t, uint64_t request_id, float q_y, flo
   a.W = d.W;
   a.sid = d.sid;
   a.tk_pack = d.tk_pack;
-  // scratch of the completed request: the C2 up links (one word per cluster)
-  // and the C4 / K5 per-row counts
-  a.un_bits = (uint32_t*)d.up0;
+  // scratch of the completed request, none of it an array that tpc_debug_copy
+  // shows: the C4 start flags (a byte per cluster) and the C4 / K5 per-row counts
+  a.un_bits = d.sflag;
   a.row_cnt = d.row_nstart;
   a.row_pos = d.k5_off;
   a.n_escaped = &d.hdr->codec_escaped;

@@ -159,3 +159,27 @@ def test_decode_windows_and_alignment(torch_cuda, lengths, shift):
     for got, ref in ((y, np.concatenate([oy[:nc], st["un_yz"][:, 0]])), (z, np.concatenate([oz[:nc], st["un_yz"][:, 1]]))):
         assert np.array_equal(got.view(np.int32), ref.astype(np.float32).view(np.int32))
     assert np.array_equal(row, np.concatenate([st["row"], st["un_row"]]))
+
+
+def test_merge_and_encode_leave_the_intermediates(torch_cuda):
+    """The arrays that the introspection call returns are those of the request, also after it was merged and encoded."""
+    from paper_2502_09138_amd import tracker as T
+    ev = synth.central_event(seed=2).sector_slice(range(2))
+    print("case: intermediates after merge and encode N=", ev.n_clusters, flush=True)
+    tr = T.Tracker(default_config(), max_clusters=ev.n_clusters, max_sectors=2)
+    rid = tr.submit(ev.y, ev.z, ev.row_offsets, ev.sector_z_lo, ev.sector_z_hi, host=True)
+    try:
+        tr.get(rid)
+        arrays = {k: getattr(T, k) for k in dir(T) if k.startswith("TPC_DBG_")}
+        before = {k: tr.debug(v, np.int32) for k, v in arrays.items()}
+        tr.merge(rid, [0, 1])
+        first = tr.encode(rid, 0.01, 0.015)[0]
+        again = tr.encode(rid, 0.01, 0.015)[0]
+        after = {k: tr.debug(v, np.int32) for k, v in arrays.items()}
+    finally:
+        tr.release(rid)
+        tr.close()
+    assert len(arrays) >= 14
+    assert [k for k in arrays if not np.array_equal(before[k], after[k])] == []
+    for k in first:
+        assert np.array_equal(first[k].cpu().numpy(), again[k].cpu().numpy()), k
