@@ -10,18 +10,19 @@
 // collects the hits in its two windows as short lists (a byte per hit, its
 // place in the run) and then tests the pairs of the two lists.  Tiles whose run
 // is larger than the stage, or with more candidates than a list holds, are left
-// to a second kernel with a larger stage (a wave takes 20 KB of LDS there), and
-// what fits neither searches the rows in global memory.
+// to a second kernel with a larger stage (a wave takes 20 KB of LDS there) and
+// longer lists, which it fills as often as it takes; a run that is larger than
+// that stage too is walked in global memory, with the same lists.
 //
 // Bound: vector instruction issue.  A wave runs as long as its longest lane,
 // so what counts is that the pair test (20 instructions) runs for the largest
 // list of the wave and not for every candidate that any lane passes, and that
 // a passing candidate costs one byte store and not a predicated write to each
 // of 4 or 8 register slots.  With such slots, loads that could be of either
-// memory, and every tile beyond the stage searched in global memory, the pass
-// took 2262 us on the 512 uneven chunks (1100 now), 365 us on the 32-orbit
-// frame (258), 106 us on the central event (60) and 245 us on one sector of
-// 210k clusters (70).
+// memory, and every tile beyond the small stage searched in global memory, the
+// pass took 2300 us on 512 chunks of 1k to 200k clusters (19M in all; 1140
+// now), 373 us on the 32-orbit frame (261), 107 us on the central event (63)
+// and 245 us on one sector of 210k clusters (69).
 //
 // All window tests and the pair deviation use float32 with contraction off, in
 // the order the definition writes them, so the argmin is bit-identical to any
@@ -35,18 +36,19 @@ namespace tpc {
 namespace {
 
 constexpr int kThreads = 64;             // one wave; one hit per lane
-// What a wave stages per adjacent row (hits, bins), the length of its lists and the waves per SIMD it is held to.
-// Two sizes (the tuning knob TPC_KNOB_LINK_SLOTS: 4 and 8 for sparse and dense rows), and a third for the tiles that
-// fit neither.
-template <uint32_t kHits_, uint32_t kBins_, int kLen_, int kWaves_, class Place_>
+// What a wave stages per adjacent row (hits, bins), the length of its lists, the upper hits that it tests together and the
+// waves per SIMD it is held to.  Two sizes (the tuning knob TPC_KNOB_LINK_SLOTS: 4 and 8 for sparse and dense rows), and a
+// third for the tiles that fit neither.
+template <uint32_t kHits_, uint32_t kBins_, int kLen_, int kUp_, int kWaves_, class Place_>
 struct Shape {
   static constexpr uint32_t kHits = kHits_, kBins = kBins_;
-  static constexpr int kLen = kLen_, kWaves = kWaves_;
-  using Place = Place_;   // a hit's place in the stage
+  static constexpr int kLen = kLen_, kUp = kUp_, kWaves = kWaves_;
+  static_assert(kLen % kUp == 0, "the upper list is read in whole groups");
+  using Place = Place_;   // a hit's place in the stage, or in its row
 };
-using Sparse = Shape<256, 128, 8, 7, uint8_t>;      // 5.7 KB of LDS
-using Dense = Shape<256, 256, 12, 6, uint8_t>;      // 6.8 KB
-using Large = Shape<640, 512, 32, 1, uint16_t>;     // 20.6 KB
+using Sparse = Shape<256, 128, 8, 4, 7, uint8_t>;      // 5.7 KB of LDS
+using Dense = Shape<256, 256, 12, 4, 6, uint8_t>;      // 6.8 KB
+using Large = Shape<640, 512, 32, 8, 1, uint16_t>;     // 20.6 KB
 
 constexpr int kGroup = 6;       // candidates tested at a time (4: +3% on the 32-orbit frame)
 constexpr int kRunBins = 3;     // z-lines of at most this many bins are searched as one run (see K5's search)
@@ -126,91 +128,83 @@ __device__ __forceinline__ Slice stage_row(const DevPtrs& d, uint32_t sr, float 
   return v;
 }
 
-// Places of the staged hits within the window of h, ascending, to the lane's
-// list; their number (the list holds the first kLen).
-template <class Sh>
-__device__ __forceinline__ int collect(const Slice& v, const float2* yz, const uint16_t* bs, float2 h, float wy, float wz,
-                                       typename Sh::Place (*list)[kThreads]) {
+// Where an adjacent row is read: hits by place, starts of its bins as places.
+struct Staged {
+  const float2* yz;
+  const uint16_t* bs;
+  int bofs;         // first staged bin
+  __device__ __forceinline__ uint32_t start(int b) const { return bs[b - bofs]; }
+};
+struct InRow {      // the whole row, in global memory
+  const float2* yz;
+  const uint32_t* bs;
+  uint32_t off;     // global sorted position of yz[0]
+  __device__ __forceinline__ uint32_t start(int b) const { return bs[b] - off; }
+};
+
+// A lane's walk over the hits of the bins that cover the window of h, in ascending place.
+struct Walk {
+  uint32_t q, hi;   // of the run of bins [b0, b1]
+  int b0, b1, e;    // e: the window's last bin
+};
+template <class Row>
+__device__ __forceinline__ Walk walk_of(const Row& row, const Grid& g, float2 h, float wy, float wz) {
+  const Window w = window_of(g, h.x, h.y, wy, wz);
+  Walk k;
+  k.b0 = w.iz0 * g.ny + w.iy0;
+  k.e = w.iz1 * g.ny + w.iy1;
+  k.b1 = g.ny <= kRunBins ? k.e : k.b0 + (w.iy1 - w.iy0);
+  k.q = row.start(k.b0);
+  k.hi = row.start(k.b1 + 1);
+  return k;
+}
+// The next group of hits of the walk: fn(place, pass, hit).  false at its end.
+template <class Row, class Fn>
+__device__ __forceinline__ bool next_group(Walk& k, const Row& row, int ny, float2 h, float wy, float wz, Fn fn) {
 #pragma clang fp contract(off)
+  while (k.q >= k.hi && k.b1 < k.e) {
+    k.b0 += ny;
+    k.b1 += ny;
+    k.q = row.start(k.b0);
+    k.hi = row.start(k.b1 + 1);
+  }
+  if (k.q >= k.hi) return false;
+  float2 c[kGroup];   // past the run's end: the stage's slack, or the arrays after the hits in the workspace
+#pragma unroll
+  for (int j = 0; j < kGroup; ++j) c[j] = row.yz[k.q + j];
+  const uint32_t left = k.hi - k.q;
+#pragma unroll
+  for (int j = 0; j < kGroup; ++j) fn(k.q + j, (uint32_t)j < left & fabsf(c[j].x - h.x) <= wy & fabsf(c[j].y - h.y) <= wz);
+  k.q += kGroup;
+  return true;
+}
+
+// The hits within the window of h to the lane's list; their number (the list holds the first kLen).
+template <class Sh>
+__device__ __forceinline__ int collect(const Staged& row, const Grid& g, float2 h, float wy, float wz,
+                                       typename Sh::Place (*list)[kThreads]) {
   const uint32_t lane = threadIdx.x;
-  const Window w = window_of(v.g, h.x, h.y, wy, wz);
-  const int ny = v.g.ny;
-  int b0 = w.iz0 * ny + w.iy0 - v.bofs;
-  const int e = w.iz1 * ny + w.iy1 - v.bofs;
-  int b1 = ny <= kRunBins ? e : b0 + (w.iy1 - w.iy0);
-  uint32_t q = bs[b0], hi = bs[b1 + 1];
+  Walk k = walk_of(row, g, h, wy, wz);
   int n = 0;
-  for (;;) {
-    while (q >= hi && b1 < e) {
-      b0 += ny;
-      b1 += ny;
-      q = bs[b0];
-      hi = bs[b1 + 1];
-    }
-    if (q >= hi) break;
-    float2 c[kGroup];
-#pragma unroll
-    for (int j = 0; j < kGroup; ++j) c[j] = yz[q + j];
-    const uint32_t left = hi - q;
-#pragma unroll
-    for (int j = 0; j < kGroup; ++j) {
-      const bool pass = (uint32_t)j < left & fabsf(c[j].x - h.x) <= wy & fabsf(c[j].y - h.y) <= wz;
-      if (pass & n < Sh::kLen) list[n][lane] = (typename Sh::Place)(q + j);
-      n += pass ? 1 : 0;
-    }
-    q += kGroup;
+  while (next_group(k, row, g.ny, h, wy, wz, [&](uint32_t q, bool pass) {
+    if (pass & n < Sh::kLen) list[n][lane] = (typename Sh::Place)q;
+    n += pass ? 1 : 0;
+  })) {
   }
   return n;
 }
-
-// ---- rows in global memory ----
-struct RowView {
-  Grid g;
-  const float2* yz;        // the row's hits
-  const uint32_t* bs;      // its bin starts (global positions)
-  uint32_t off;            // global sorted position of yz[0]
-};
-__device__ __forceinline__ RowView row_view(const DevPtrs& d, uint32_t sr) {
-  const RowConst& rc = d.rows[sr % d.R];
-  const SectorConst& sc = d.secs[sr / d.R];
-  const uint2 meta = d.row_meta[sr];
-  return RowView{Grid{(int)(meta.y & 0xFFFFu), (int)(meta.y >> 16), rc.y_lo, rc.inv_wy, sc.z_lo, sc.inv_wz},
-                 d.syz + d.row_off[sr], d.bin_start + meta.x, d.row_off[sr]};
-}
-
-// fn(q, (y, z)) for every hit q (relative to v.off) of the bins covering a window around h, ascending.
-template <class Fn>
-__device__ __forceinline__ void for_window(const RowView& v, float2 h, float wy, float wz, Fn fn) {
-  const Window w = window_of(v.g, h.x, h.y, wy, wz);
-  for (int iz = w.iz0; iz <= w.iz1; ++iz) {
-    const uint32_t hi = v.bs[iz * v.g.ny + w.iy1 + 1] - v.off;
-    for (uint32_t q = v.bs[iz * v.g.ny + w.iy0] - v.off; q < hi; ++q) {
-      const float2 c = v.yz[q];
-      if (fabsf(c.x - h.x) <= wy && fabsf(c.y - h.y) <= wz) fn(q, c);
-    }
+// The next of them, while a whole group still fits the list.
+template <class Sh, class Row>
+__device__ __forceinline__ int collect_some(Walk& k, const Row& row, const Grid& g, float2 h, float wy, float wz,
+                                            typename Sh::Place (*list)[kThreads]) {
+  const uint32_t lane = threadIdx.x;
+  int n = 0;
+  while (n <= Sh::kLen - kGroup && next_group(k, row, g.ny, h, wy, wz, [&](uint32_t q, bool pass) {
+    if (pass) list[n][lane] = (typename Sh::Place)q;
+    n += pass ? 1 : 0;
+  })) {
   }
-}
-
-// Links of the hit at sorted position p of row sr, any number of candidates.
-__device__ __forceinline__ void link_global(const DevPtrs& d, uint32_t p, uint32_t sr, float rho) {
-  const RowConst& rc = d.rows[sr % d.R];
-  const RowView dn = row_view(d, sr - 1), up = row_view(d, sr + 1);
-  const float2 h = d.syz[p];
-  int32_t bu = -1, bd = -1;
-  float best = rc.dmax;
-  for_window(dn, h, rc.wy_dn, rc.wz_dn, [&](uint32_t qd, float2 pd) {
-    for_window(up, h, rc.wy_up, rc.wz_up, [&](uint32_t qu, float2 pu) {
-      const float dev = deviation(h, pd, pu, rc.t, rho);
-      const int32_t gu = (int32_t)(up.off + qu);
-      if (dev < best || (dev == best && (bu < 0 || gu < bu))) {   // down positions ascend
-        best = dev;
-        bu = gu;
-        bd = (int32_t)(dn.off + qd);
-      }
-    });
-  });
-  d.up0[p] = bu;
-  d.down0[p] = bd;
+  return n;
 }
 
 // Minimum over the wave (NaN ignored).
@@ -227,78 +221,119 @@ __device__ __forceinline__ float wave_minf(float v) {
   return fminf(fminf(lane(0), lane(16)), fminf(lane(32), lane(48)));
 }
 
-// Links of one tile.  Tiles that do not fit the shape (a run larger than the
-// stage, a list longer than its lanes hold) search in global memory, or with
-// kRetry are left: false, and nothing is written.
-template <class Sh, bool kRetry>
-__device__ __forceinline__ bool link_tile(const DevPtrs& d, uint32_t tile, float rho, Stage<Sh>& S) {
-  const uint32_t sr = d.tile_sr[tile], R = d.R, row = sr % R;
-  const uint32_t a = d.row_off[sr] + (tile - d.tile_off[sr]) * kThreads;
-  const uint32_t cnt = min((uint32_t)kThreads, d.row_off[sr + 1] - a);
+// Every pair of the first nd of the lower list and the first nu of the upper one, kUp of the upper hits at a time in
+// registers against every lower one.  Called by the whole wave.
+template <class Sh, class Row>
+__device__ __forceinline__ void test_pairs(const Stage<Sh>& S, const Row& dn, const Row& up, int nd, int nu, float2 h, float t,
+                                           float rho, Best& best) {
+  constexpr int kUp = Sh::kUp;
   const uint32_t lane = threadIdx.x;
-  const bool mine = lane < cnt;
-  const uint32_t p = a + lane;
-  if (row == 0 || row + 1 >= R) {
-    if (mine) {
-      d.up0[p] = -1;
-      d.down0[p] = -1;
+  for (int u0 = 0; __any(u0 < nu && nd > 0); u0 += kUp) {
+    uint32_t qu[kUp];
+    float2 pu[kUp];
+#pragma unroll
+    for (int k = 0; k < kUp; ++k) {
+      const uint32_t q = S.list[1][u0 + k][lane];
+      qu[k] = u0 + k < nu ? q : 0u;
     }
-    return true;
-  }
-  const float2 h = mine ? d.syz[p] : make_float2(0.0f, 0.0f);
-  const float zmin = wave_minf(mine ? h.y : INFINITY), zmax = -wave_minf(mine ? -h.y : INFINITY);
-  // a non-finite or out-of-range z (flagged by K1) has no place in the z-line
-  // order: such a tile searches the adjacent rows in global memory
-  const bool stage = !__any(mine && !(fabsf(h.y) <= kMaxCoord));
-  const RowConst rc = d.rows[row];
-  const Slice dn = stage_row<Sh>(d, sr - 1, zmin, zmax, rc.wz_dn, stage, S.yz[0], S.bs[0]);
-  const Slice up = stage_row<Sh>(d, sr + 1, zmin, zmax, rc.wz_up, stage, S.yz[1], S.bs[1]);
-  __syncthreads();
-  bool global = mine;
-  Best best{rc.dmax, kNone, kNone};
-  if (dn.staged && up.staged) {   // wave-uniform
-    const int nu = mine ? collect<Sh>(up, S.yz[1], S.bs[1], h, rc.wy_up, rc.wz_up, S.list[1]) : 0;
-    const int nd = nu > 0 ? collect<Sh>(dn, S.yz[0], S.bs[0], h, rc.wy_dn, rc.wz_dn, S.list[0]) : 0;
-    global = nu > Sh::kLen || nd > Sh::kLen;
-    // four of the upper hits at a time in registers against every lower one
-    constexpr int kUp = 4;
-    const int pairs_u = global ? 0 : nu, pairs_d = global ? 0 : nd;
-    for (int u0 = 0; __any(u0 < pairs_u && pairs_d > 0); u0 += kUp) {
-      uint32_t qu[kUp];
-      float2 pu[kUp];
+#pragma unroll
+    for (int k = 0; k < kUp; ++k) pu[k] = up.yz[qu[k]];
+    for (int kd = 0; __any(kd < nd && u0 < nu); ++kd) {
+      const uint32_t q = S.list[0][kd][lane], qd = kd < nd ? q : 0u;
+      const float2 pd = dn.yz[qd];
 #pragma unroll
       for (int k = 0; k < kUp; ++k) {
-        const uint32_t q = S.list[1][u0 + k][lane];
-        qu[k] = u0 + k < pairs_u ? q : 0u;
-      }
-#pragma unroll
-      for (int k = 0; k < kUp; ++k) pu[k] = S.yz[1][qu[k]];
-      for (int kd = 0; __any(kd < pairs_d && u0 < pairs_u); ++kd) {
-        const uint32_t q = S.list[0][kd][lane], qd = kd < pairs_d ? q : 0u;
-        const float2 pd = S.yz[0][qd];
-#pragma unroll
-        for (int k = 0; k < kUp; ++k) {
-          const float dev = deviation(h, pd, pu[k], rc.t, rho);
-          // lower hits ascend, so of two pairs with the same upper hit the first has the smaller lower one
-          const bool take = kd < pairs_d & u0 + k < pairs_u & (dev < best.dev | (dev == best.dev & qu[k] < best.u));
-          best.dev = take ? dev : best.dev;
-          best.u = take ? qu[k] : best.u;
-          best.d = take ? qd : best.d;
-        }
+        const float dev = deviation(h, pd, pu[k], t, rho);
+        // lower hits ascend, so of two pairs with the same upper hit the first has the smaller lower one
+        const bool take = kd < nd & u0 + k < nu & (dev < best.dev | (dev == best.dev & qu[k] < best.u));
+        best.dev = take ? dev : best.dev;
+        best.u = take ? qu[k] : best.u;
+        best.d = take ? qd : best.d;
       }
     }
   }
-  if (kRetry && __any(global)) return false;
-  if (global) {
-    link_global(d, p, sr, rho);
-  } else if (mine) {
-    d.up0[p] = best.u == kNone ? -1 : (int32_t)(up.off + best.u);
-    d.down0[p] = best.u == kNone ? -1 : (int32_t)(dn.off + best.d);
+}
+
+// The best pair of the two windows, however many hits they hold: a list of upper hits after the other, and against each
+// of them the lower hits a list at a time.  Called by the whole wave.
+template <class Sh, class Row>
+__device__ __forceinline__ void test_windows(Stage<Sh>& S, const Row& dn, const Row& up, const Grid& gd, const Grid& gu,
+                                             bool mine, float2 h, const RowConst& rc, float rho, Best& best) {
+  Walk wu{0u, 0u, 0, 0, 0};
+  if (mine) wu = walk_of(up, gu, h, rc.wy_up, rc.wz_up);
+  for (;;) {
+    const int nu = mine ? collect_some<Sh>(wu, up, gu, h, rc.wy_up, rc.wz_up, S.list[1]) : 0;
+    if (!__any(nu > 0)) break;   // a walk ends its list early only at its own end
+    Walk wd{0u, 0u, 0, 0, 0};
+    if (nu > 0) wd = walk_of(dn, gd, h, rc.wy_dn, rc.wz_dn);
+    for (;;) {
+      const int nd = nu > 0 ? collect_some<Sh>(wd, dn, gd, h, rc.wy_dn, rc.wz_dn, S.list[0]) : 0;
+      if (!__any(nd > 0)) break;
+      test_pairs(S, dn, up, nd, nu, h, rc.t, rho, best);
+    }
   }
+}
+
+// A tile: its row, the row's constants and the lane's hit.
+struct Tile {
+  uint32_t sr, p;   // (sector, row), the lane's sorted position
+  bool mine, edge;  // the lane has a hit; the row is the first or the last
+};
+__device__ __forceinline__ Tile tile_of(const DevPtrs& d, uint32_t tile) {
+  Tile t;
+  t.sr = d.tile_sr[tile];
+  const uint32_t R = d.R, row = t.sr % R;
+  const uint32_t a = d.row_off[t.sr] + (tile - d.tile_off[t.sr]) * kThreads;
+  t.mine = threadIdx.x < min((uint32_t)kThreads, d.row_off[t.sr + 1] - a);
+  t.p = a + threadIdx.x;
+  t.edge = row == 0 || row + 1 >= R;
+  return t;
+}
+
+__device__ __forceinline__ void write_links(const DevPtrs& d, const Tile& t, const Best& best, uint32_t off_up, uint32_t off_dn) {
+  if (!t.mine) return;
+  d.up0[t.p] = best.u == kNone ? -1 : (int32_t)(off_up + best.u);
+  d.down0[t.p] = best.u == kNone ? -1 : (int32_t)(off_dn + best.d);
+}
+
+// The two adjacent rows' slices of a tile.
+template <class Sh>
+__device__ __forceinline__ void stage_tile(const DevPtrs& d, const Tile& t, const RowConst& rc, float2 h, Stage<Sh>& S, Slice& dn,
+                                           Slice& up) {
+  const float zmin = wave_minf(t.mine ? h.y : INFINITY), zmax = -wave_minf(t.mine ? -h.y : INFINITY);
+  // a non-finite or out-of-range z (flagged by K1) has no place in the z-line
+  // order: such a tile searches the adjacent rows in global memory
+  const bool stage = !__any(t.mine && !(fabsf(h.y) <= kMaxCoord));
+  dn = stage_row<Sh>(d, t.sr - 1, zmin, zmax, rc.wz_dn, stage, S.yz[0], S.bs[0]);
+  up = stage_row<Sh>(d, t.sr + 1, zmin, zmax, rc.wz_up, stage, S.yz[1], S.bs[1]);
+  __syncthreads();
+}
+
+// Links of one tile; false, and nothing written, where a run is larger than the stage or a list longer than its lanes hold.
+template <class Sh>
+__device__ __forceinline__ bool link_tile(const DevPtrs& d, uint32_t tile, float rho, Stage<Sh>& S) {
+  const Tile t = tile_of(d, tile);
+  Best best{0.0f, kNone, kNone};
+  if (t.edge) {
+    write_links(d, t, best, 0u, 0u);
+    return true;
+  }
+  const float2 h = t.mine ? d.syz[t.p] : make_float2(0.0f, 0.0f);
+  const RowConst rc = d.rows[t.sr % d.R];
+  Slice dn, up;
+  stage_tile(d, t, rc, h, S, dn, up);
+  if (!(dn.staged && up.staged)) return false;   // wave-uniform
+  const Staged rd{S.yz[0], S.bs[0], dn.bofs}, ru{S.yz[1], S.bs[1], up.bofs};
+  const int nu = t.mine ? collect<Sh>(ru, up.g, h, rc.wy_up, rc.wz_up, S.list[1]) : 0;
+  const int nd = nu > 0 ? collect<Sh>(rd, dn.g, h, rc.wy_dn, rc.wz_dn, S.list[0]) : 0;
+  if (__any(nu > Sh::kLen || nd > Sh::kLen)) return false;
+  best.dev = rc.dmax;
+  test_pairs(S, rd, ru, nd, nu, h, rc.t, rho, best);
+  write_links(d, t, best, up.off, dn.off);
   return true;
 }
 
-template <class Sh, bool kRetry>
+template <class Sh>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(Sh::kWaves)))
 k_links(DevPtrs d, float rho, uint32_t G) {
   __shared__ Stage<Sh> S;
@@ -309,39 +344,53 @@ k_links(DevPtrs d, float rho, uint32_t G) {
   const uint32_t l = blockIdx.x / kXcds;
   const uint32_t tile = G <= 1 ? blockIdx.x : ((l / G) * kXcds + blockIdx.x % kXcds) * G + l % G;
   if (tile >= d.n_link_tiles) return;
-  if (!link_tile<Sh, kRetry>(d, tile, rho, S) && threadIdx.x == 0)
+  if (!link_tile<Sh>(d, tile, rho, S) && threadIdx.x == 0)
     d.link_retry[atomicAdd(&d.hdr->link_retries, 1u)] = tile;
 }
 
-// The tiles that k_links left, with the large stage: dense rows (a chunk of
-// 200k clusters has 1300 hits a row, most of them in the third of the drift
-// range that its particles reach at the inner rows).
+// The tiles that k_links left: dense rows (a chunk of 200k clusters has 1300
+// hits a row, most of them in the third of the drift range that its particles
+// reach at the inner rows) and crowded or wide windows.  The pass takes 481 us
+// on one sector of 483k clusters (3400 hits a row, some 20 in a window), 2312
+// on one of 969k, and 1058 on two sectors of rows of 600 hits in a patch of 20
+// by 25 cm.  Walking the upper window in global memory for every lower hit of
+// such a tile took 2238, 15093 and 22932.  Where no tile was left the launch
+// costs 2 us.
 __global__ void __launch_bounds__(kThreads) k_links_large(DevPtrs d, float rho) {
   __shared__ Stage<Large> S;
   const uint32_t n = d.hdr->link_retries;
   for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
-    link_tile<Large, false>(d, d.link_retry[i], rho, S);
+    const Tile t = tile_of(d, d.link_retry[i]);   // never of the first or the last row
+    const float2 h = t.mine ? d.syz[t.p] : make_float2(0.0f, 0.0f);
+    const RowConst rc = d.rows[t.sr % d.R];
+    Slice dn, up;
+    stage_tile(d, t, rc, h, S, dn, up);
+    Best best{rc.dmax, kNone, kNone};
+    if (dn.staged && up.staged) {
+      test_windows(S, Staged{S.yz[0], S.bs[0], dn.bofs}, Staged{S.yz[1], S.bs[1], up.bofs}, dn.g, up.g, t.mine, h, rc, rho, best);
+    } else {
+      dn.off = d.row_off[t.sr - 1];
+      up.off = d.row_off[t.sr + 1];
+      test_windows(S, InRow{d.syz + dn.off, d.bin_start + d.row_meta[t.sr - 1].x, dn.off},
+                   InRow{d.syz + up.off, d.bin_start + d.row_meta[t.sr + 1].x, up.off}, dn.g, up.g, t.mine, h, rc, rho, best);
+    }
+    write_links(d, t, best, up.off, dn.off);
     __syncthreads();   // the stage is read to the end before the next tile fills it
   }
 }
 
 }  // namespace
 
-void launch_links(const DevPtrs& d, uint32_t max_row_hits, hipStream_t s) {
+void launch_links(const DevPtrs& d, hipStream_t s) {
   if (d.n_link_tiles == 0) return;
   // group size: as set, or one contiguous eighth of the tiles per XCD
   const uint32_t n = d.n_link_tiles;
   const uint32_t G = d.k2_group == kLinkGroupEighth ? (n + kXcds - 1) / kXcds : std::max<uint32_t>(1u, d.k2_group);
   const uint64_t groups = (n + (uint64_t)G - 1) / G;
   const uint32_t blocks = G == 1 ? n : (uint32_t)((groups + kXcds - 1) / kXcds * kXcds * G);   // every group slot
-  // rows of at most the staged hits always fit, so a tile is left only for a list that overflows: no second launch
-  if (max_row_hits <= Dense::kHits) {
-    if (d.k2_slots == 4) hipLaunchKernelGGL((k_links<Sparse, false>), dim3(blocks), dim3(kThreads), 0, s, d, d.rho, G);
-    else hipLaunchKernelGGL((k_links<Dense, false>), dim3(blocks), dim3(kThreads), 0, s, d, d.rho, G);
-    return;
-  }
-  if (d.k2_slots == 4) hipLaunchKernelGGL((k_links<Sparse, true>), dim3(blocks), dim3(kThreads), 0, s, d, d.rho, G);
-  else hipLaunchKernelGGL((k_links<Dense, true>), dim3(blocks), dim3(kThreads), 0, s, d, d.rho, G);
+  if (d.k2_slots == 4) hipLaunchKernelGGL(k_links<Sparse>, dim3(blocks), dim3(kThreads), 0, s, d, d.rho, G);
+  else hipLaunchKernelGGL(k_links<Dense>, dim3(blocks), dim3(kThreads), 0, s, d, d.rho, G);
+  // any tile may be left (a list can overflow whatever the row's size)
   hipLaunchKernelGGL(k_links_large, dim3(std::min(n, 2048u)), dim3(kThreads), 0, s, d, d.rho);
 }
 

@@ -233,7 +233,7 @@ constexpr int kScanMaxBlocks = 8192;               // supports scans of up to 8M
 
 // ---- launch wrappers (each in its own .hip file) ----
 void launch_grid(const DevPtrs& d, uint32_t max_row_hits, uint32_t max_pack_hits, hipStream_t s);
-void launch_links(const DevPtrs& d, uint32_t max_row_hits, hipStream_t s);
+void launch_links(const DevPtrs& d, hipStream_t s);
 void launch_clean_starts(const DevPtrs& d, uint32_t max_row_hits, hipStream_t s);
 hipError_t init_tracklets();   // with the device current, before the first launch_tracklets on it
 void launch_tracklets(const DevPtrs& d, const KfConst& k, uint32_t max_row_hits, hipStream_t s);

@@ -725,7 +725,7 @@ tpc_status enqueue(tpc_tracker* t, const tpc_timeframe* f, uint32_t max_row, uin
   HIP_TRY(mark(0));
   launch_grid(d, max_row, max_pack, st);
   HIP_TRY(mark(1));
-  launch_links(d, max_row, st);
+  launch_links(d, st);
   HIP_TRY(mark(2));
   launch_clean_starts(d, max_row, st);
   HIP_TRY(mark(3));
