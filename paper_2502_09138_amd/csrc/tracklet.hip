@@ -806,6 +806,7 @@ __global__ void __launch_bounds__(kOrderThreads) k_order(DevPtrs d) {
   const uint32_t first = min(need, blockIdx.x * per), b1 = min(need, first + per);
   const uint32_t b0 = kDown && b1 - first > kOrdered ? b1 : b1 - min(b1 - first, kOrdered), tid = threadIdx.x;
   for (uint32_t b = first + tid; b < b0; b += kOrderThreads) d.k5_order[b] = b;
+  if (b0 == b1) return;   // none to sort
   uint32_t x = 0xFFFFFFFFu;
   if (b0 + tid < b1) {
     const uint32_t j0 = (b0 + tid) * kThreads, j1 = min(n, j0 + kThreads) - 1;
@@ -1841,9 +1842,12 @@ k_tracklets_res(DevPtrs d, KfConst k, ResLds l, uint32_t parts) {
   else resident_sector<2>(d, k, l, res_s, sec, part, parts);
 }
 
+constexpr uint32_t kSparse = 128;   // see launch_tracklets
+
 // Waves of the row-synchronous schedule: ceil(tracklets of sector s / per_wave)
-// per sector, prefix-summed (one block).  More than most of them: none, and the
-// tracklets are left to the pipeline.
+// per sector, prefix-summed (one block).  More than most of them, or (most
+// given) more than kSparse hits a tracklet: none, and the tracklets are left to
+// the pipeline.
 __global__ void __launch_bounds__(1024) k_waves(DevPtrs d, uint32_t per_wave, uint32_t most) {
   __shared__ uint32_t wsum[1024 / kWave];
   const uint32_t S = d.S, R = d.R, T = d.tcap;
@@ -1862,8 +1866,9 @@ __global__ void __launch_bounds__(1024) k_waves(DevPtrs d, uint32_t per_wave, ui
     run += (b - a + per_wave - 1) / per_wave;
   }
   if (threadIdx.x == 0) {
-    d.wave_off[S] = total > most ? 0 : total;
-    d.hdr->pipe_starts = total > most ? d.hdr->n_starts : 0;
+    const bool rows = most == ~0u || (total <= most && (uint64_t)d.hdr->n_starts * kSparse >= d.N);
+    d.wave_off[S] = rows ? total : 0;
+    d.hdr->pipe_starts = rows ? 0 : d.hdr->n_starts;
   }
 }
 
@@ -1876,10 +1881,16 @@ hipError_t init_tracklets() {
 
 // Frames of up to kRowSyncHits hits are swept row by row: at 12 hits a tracklet (12 to 24 were seen) the waves of one lane
 // per tracklet are all resident, two on a SIMD.  Up to kRowSyncMaybe they may be, and the device decides on the number of
-// tracklets: both schedules are launched, and one finds nothing to do (8 launches, 45 us, or 2 launches, 8 us).  Larger
+// tracklets: both schedules are launched, and one finds nothing to do (8 launches, 20 us, or 2 launches, 8 us).  Larger
 // frames go through the pipeline.  us of a call, pipeline / row by row: 4 dense sectors, 0.92M hits 1420 / 1230; 40 chunks
 // of up to 200k, 1.45M 1380 / 1260; 8 heavy-ion orbits, 2.6M, 2008 waves 1228 / 1083 (1130 here); with more waves than are resident, 8
 // dense sectors, 1.86M 1690 / 2090; 9 heavy-ion orbits, 2.9M 1268 / 1530.
+// The device also decides where rows are too large to stage and the frame may hold few tracklets for its hits (kSparse):
+// the row sweeps pass every row between a wave's first and last, and tracklets of noise are short and far apart, while
+// the pipeline's lanes end with their tracklet.  us of K5 on hits without particles, pipeline / row by row (hits a
+// tracklet): 6 sectors of 52k 203 / 625 (2000), 30 of 52k 237 / 631 (2100) and, over less drift, 275 / 346 (148), 36 of 61k 273 / 436
+// (272), 10 of 106k 284 / 308 (238), 8 of 182k 294 / 306 (71); with particles one sector of 142k 792 / 657 (12), of 969k
+// 916 / 795 (65).  Frames whose rows are staged were always swept row by row, and stay so.
 constexpr uint32_t kResidentWaves = 2048;
 constexpr uint32_t kRowSyncHits = kResidentWaves * kWave * 12;
 constexpr uint32_t kRowSyncMaybe = kResidentWaves * kWave * 24;
@@ -1895,9 +1906,11 @@ void launch_tracklets(const DevPtrs& frame, const KfConst& k, uint32_t max_row_h
   if (frame.tcap == 0) return;
   DevPtrs d = frame;
   const bool staged = max_row_hits <= (uint32_t)kStageHits;   // every row: the kernel carries no search in global memory
-  const bool maybe = d.k5_mode == 0 && d.N > kRowSyncHits && d.N <= kRowSyncMaybe;
+  const bool maybe = d.k5_mode == 0 && d.N <= kRowSyncMaybe && (d.N > kRowSyncHits || !staged);
   const bool rowsync = maybe || d.k5_mode == 2 || (d.k5_mode == 0 && d.N <= kRowSyncHits);
   d.pipe_n = maybe ? &d.hdr->pipe_starts : &d.hdr->n_starts;
+  // the pipeline of such a frame has few waves, or none: without the sort's three launches, which are 7 us where it has none
+  if (maybe && d.N <= kRowSyncHits) d.k5_refit_order = 1;
   // Resident sectors while their workgroups run side by side (three on a CU at most, by registers; about a tracklet per 16
   // hits): 60 chunks of up to 13k hits run 7% faster than row by row, 500 of up to 3k as fast, and 400 of up to 13k, one
   // workgroup on a CU at a time, 2.3 times as long.
