@@ -893,11 +893,12 @@ tpc_status tpc_merge_sectors(tpc_tracker* t, uint64_t request_id, const int32_t*
   const Layout& L = t->lay;
   const Caps& hc = t->host_caps;
   const Layout HL = layout_of(hc);   // pinned merge buffers are laid out for the create-time capacities
-  if (!t->h_merge) {
-    if (hipHostMalloc((void**)&t->h_merge, HL.m_nseg + hc.MT * 4 - HL.m_next + 16) != hipSuccess ||
-        hipHostGetDevicePointer((void**)&t->d_merge_host, t->h_merge, 0) != hipSuccess ||
-        hipHostMalloc((void**)&t->h_phys, (size_t)hc.Smax * 4) != hipSuccess)
-      return fail(TPC_E_NOMEM, "hipHostMalloc merge buffers");
+  // each on its own: a merge that got only some of them is followed by one that gets the rest
+  if ((!t->h_merge && hipHostMalloc((void**)&t->h_merge, HL.m_nseg + hc.MT * 4 - HL.m_next + 16) != hipSuccess) ||
+      (!t->d_merge_host && hipHostGetDevicePointer((void**)&t->d_merge_host, t->h_merge, 0) != hipSuccess) ||
+      (!t->h_phys && hipHostMalloc((void**)&t->h_phys, (size_t)hc.Smax * 4) != hipSuccess)) {
+    (void)hipGetLastError();   // reported here, not by the next launch
+    return fail(TPC_E_NOMEM, "hipHostMalloc merge buffers");
   }
   char* w = t->ws;
   MergeArgs m{};
