@@ -148,3 +148,79 @@ def test_merge_candidates_over_sizes_and_windows(torch_cuda, n_tracks, windows):
     g_links = {(int(start[a]), int(start[b])) for a, b in enumerate(mg["next"]) if b >= 0}
     print("links", len(o_links), len(g_links), "common", len(o_links & g_links), flush=True)
     assert len(o_links ^ g_links) <= max(1, 0.005 * len(o_links))
+
+
+def _links_over_all_pairs(sector, x_ref, param, cov, phys, cfg):
+    """C8 in double over every pair of the given tracks, without a candidate list: next[] (-1: none)."""
+    n, p = len(sector), param.astype(np.float64)
+    x, phys = x_ref.astype(np.float64), np.asarray(phys)
+    cyy, czz = cov[:, 0].astype(np.float64), cov[:, 2].astype(np.float64)
+    r_in = np.sqrt(x * x + p[:, 0] * p[:, 0])
+    bk, smax = -0.00299792458 * cfg.bz, cfg.s_max
+    succ, succ_score = np.full(n, -1), np.full(n, np.inf)
+    pred, pred_score = np.full(n, -1), np.full(n, np.inf)
+    for a in range(n):
+        ph = int(phys[sector[a]])
+        for step in (-1, 1) if ph >= 0 else ():
+            where = np.flatnonzero(phys == ph // 18 * 18 + (ph % 18 + step) % 18)
+            if not len(where):
+                continue
+            b = np.flatnonzero((sector == where[0]) & (r_in > r_in[a]))
+            d = step * np.deg2rad(20.0)
+            y, z, s, t, k = p[a]
+            cs = np.sqrt((1 - s) * (1 + s))
+            s1, c1 = s * np.cos(d) - cs * np.sin(d), cs * np.cos(d) + s * np.sin(d)
+            if not (c1 > 0 and abs(s1) < smax):
+                continue
+            dx = x[b] - (x[a] * np.cos(d) + y * np.sin(d))
+            s2 = s1 + bk * k * dx
+            b, dx, s2 = (v[np.abs(s2) < smax] for v in (b, dx, s2))
+            dy = dx * (s1 + s2) / (np.sqrt((1 - s1) * (1 + s1)) + np.sqrt((1 - s2) * (1 + s2)))
+            L = np.sqrt(dx * dx + dy * dy)
+            u = 0.5 * bk * k * L
+            b, dx, s2, dy, L, u = (v[np.abs(u) < 1] for v in (b, dx, s2, dy, L, u))
+            S = np.sign(dx) * L * np.where(u == 0, 1.0, np.arcsin(u) / np.where(u == 0, 1.0, u))
+            dy = -x[a] * np.sin(d) + y * np.cos(d) + dy - p[b, 0]
+            dz = z + t * S - p[b, 1]
+            ok = ((np.abs(dy) <= cfg.merge_dy) & (np.abs(dz) <= cfg.merge_dz) & (np.abs(s2 - p[b, 2]) <= cfg.merge_dsinphi) &
+                  (np.abs(t - p[b, 3]) <= cfg.merge_dtanl) & (np.abs(k - p[b, 4]) <= cfg.merge_dqpt))
+            score = dy * dy / (cyy[b] + cfg.sigma_y ** 2) + dz * dz / (czz[b] + cfg.sigma_z ** 2)
+            for j, sc in zip(b[ok], score[ok]):   # ascending j; a ascends, too
+                if sc < succ_score[a] or (sc == succ_score[a] and j < succ[a]):
+                    succ[a], succ_score[a] = j, sc
+                if sc < pred_score[j]:
+                    pred[j], pred_score[j] = a, sc
+    return np.array([s if s >= 0 and pred[s] == a else -1 for a, s in enumerate(succ)], np.int64)
+
+
+@pytest.mark.parametrize("n_tracks, windows, at_least",
+                         [(1, {}, 1), (3, {}, 2), (30, {}, 10), (60, dict(merge_dtanl=10.0, merge_dqpt=100.0, merge_dz=1e4), 20),
+                          (200, dict(merge_dtanl=1 / 64, merge_dqpt=0.1), 40), (300, dict(merge_dtanl=1e-3, merge_dz=0.3), 10),
+                          (700, {}, 200), (1500, dict(merge_dtanl=0.3, merge_dz=20.0, merge_dsinphi=0.2, merge_dy=6.0), 300)])
+def test_merge_links_are_those_of_all_pairs(torch_cuda, n_tracks, windows, at_least):
+    """The links exactly, against a walk over every pair of the GPU's own tracks in double: no candidate may be lost by the
+    tan(lambda) bins or the reach in z.  Chains, their cluster lists and single segments' results with them."""
+    from paper_2502_09138_amd.tracker import Tracker
+    ev = synth.boundary_crossers(seed=11, n_tracks=n_tracks)
+    print("case: merge over all pairs", n_tracks, windows, "N=", ev.n_clusters, flush=True)
+    cfg = default_config(**windows)
+    tr = Tracker(cfg, max_clusters=max(64, ev.n_clusters), max_sectors=ev.n_sectors)
+    tracks, mg = tr.track_and_merge(ev.y, ev.z, ev.row_offsets, ev.sector_z_lo, ev.sector_z_hi, [0, 1, 2], host=True)
+    tr.close()
+    ref = _links_over_all_pairs(tracks.sector, tracks.x_ref, tracks.param, tracks.cov, [0, 1, 2], cfg)
+    print("tracks", tracks.n_tracks, "links", int((ref >= 0).sum()), flush=True)
+    assert (ref >= 0).sum() >= at_least
+    assert np.array_equal(mg["next"], ref)
+    heads = np.setdiff1d(np.arange(tracks.n_tracks), ref)
+    assert np.array_equal(mg["heads"], heads) and len(mg["first"]) == len(heads) + 1
+    for c, h in enumerate(heads):
+        chain = [int(h)]
+        while ref[chain[-1]] >= 0:
+            chain.append(int(ref[chain[-1]]))
+        ids = np.concatenate([tracks.cluster_ids[tracks.first[t]:tracks.first[t + 1]] for t in chain])
+        assert np.array_equal(mg["clusters"][mg["first"][c]:mg["first"][c + 1]], ids)
+        assert mg["nseg"][c] == len(chain) and np.all(mg["head_of"][chain] == h)
+        assert mg["ndf"][c] in ((2 * len(ids) - 5,) if len(chain) == 1 else (2 * len(ids) - 5, -1))
+        if len(chain) == 1 or mg["ndf"][c] == -1:
+            assert np.array_equal(mg["param"][c], tracks.param[h]) and np.array_equal(mg["cov"][c], tracks.cov[h])
+            assert mg["chi2"][c] == tracks.chi2[h]
