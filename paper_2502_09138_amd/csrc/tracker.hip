@@ -647,7 +647,7 @@ tpc_status enqueue(tpc_tracker* t, const tpc_timeframe* f, uint32_t max_row, uin
   for (uint32_t s = 0; s < S; ++s) {
     const uint32_t n = f->row_offsets[(s + 1) * R] - f->row_offsets[s * R];
     d.max_sector_hits = std::max(d.max_sector_hits, n);
-    d.res_blocks += (n + 16 * 128 - 1) / (16 * 128);
+    d.res_blocks += std::max(1u, (n + 16 * 128 - 1) / (16 * 128));   // also a sector without hits has a workgroup
   }
   hipStream_t st = t->stream;   // the previous request was released, so the staging buffers are free
   if (f->flags & TPC_IN_HOST) {

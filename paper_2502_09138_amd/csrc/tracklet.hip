@@ -1836,9 +1836,13 @@ k_tracklets_res(DevPtrs d, KfConst k, ResLds l, uint32_t parts) {
   // spread over the XCDs and CUs
   const uint32_t sec = blockIdx.x % d.S, part = blockIdx.x / d.S;
   const uint32_t n = min(d.hdr->n_starts, d.tcap);
-  if (n * 16 <= kLanesAlone) resident_sector<16>(d, k, l, res_s, sec, part, parts);
-  else if (n * 8 <= kLanesAlone) resident_sector<8>(d, k, l, res_s, sec, part, parts);
-  else if (n * 4 <= kLanesAlone) resident_sector<4>(d, k, l, res_s, sec, part, parts);
+  const uint32_t own = min(d.row_start_off[(sec + 1) * d.R], d.tcap) - min(d.row_start_off[sec * d.R], d.tcap);
+  // the most lanes that leave every wave alone on its SIMD, and the sector's parts room for its tracklets at once: a second
+  // round takes as long as the first (one sector of 13k hits among 399 without hits 1832 us a call at 16 lanes, 745 at two)
+  auto lanes = [&](uint32_t kL) { return n * kL <= kLanesAlone && own * kL <= parts * kResThreads; };
+  if (lanes(16)) resident_sector<16>(d, k, l, res_s, sec, part, parts);
+  else if (lanes(8)) resident_sector<8>(d, k, l, res_s, sec, part, parts);
+  else if (lanes(4)) resident_sector<4>(d, k, l, res_s, sec, part, parts);
   else resident_sector<2>(d, k, l, res_s, sec, part, parts);
 }
 
@@ -1913,11 +1917,14 @@ void launch_tracklets(const DevPtrs& frame, const KfConst& k, uint32_t max_row_h
   if (maybe && d.N <= kRowSyncHits) d.k5_refit_order = 1;
   // Resident sectors while their workgroups run side by side (three on a CU at most, by registers; about a tracklet per 16
   // hits): 60 chunks of up to 13k hits run 7% faster than row by row, 500 of up to 3k as fast, and 400 of up to 13k, one
-  // workgroup on a CU at a time, 2.3 times as long.
+  // workgroup on a CU at a time, 2.3 times as long.  Every sector has as many parts as the fullest one needs at two lanes
+  // a tracklet: no more than 1024 in all, of which most have nothing to do where one sector is full and the others are not
+  // (us of a call, row by row / resident: one of 13k hits among 99 of 700 661 / 618, two among 198 of 600 785 / 914).
   const ResLds l = res_lds(std::max(1u, d.max_sector_hits), max_row_hits, d.R, (uint32_t)d.grid_k);
-  if (d.k5_mode != 1 && l.total && d.res_blocks <= 256u * std::min(3u, kResLdsBytes / l.total)) {
+  const uint32_t full = (d.max_sector_hits / 16 + kResPer - 1) / kResPer;
+  if (d.k5_mode != 1 && l.total && d.res_blocks <= 256u * std::min(3u, kResLdsBytes / l.total) && (uint64_t)d.S * full <= 1024u) {
     // a sector with more tracklets than its parts hold loops
-    const uint32_t parts = std::max((768u + d.S - 1) / d.S, (d.max_sector_hits / 16 + kResPer - 1) / kResPer);
+    const uint32_t parts = std::max((768u + d.S - 1) / d.S, full);
     hipLaunchKernelGGL(k_tracklets_res, dim3(d.S * parts), dim3(kResThreads), l.total, s, d, k, l, parts);
     return;
   }

@@ -200,3 +200,56 @@ def test_sparse_frames_are_not_swept_row_by_row(sectors, per_row):
         for k in FIELDS:
             np.testing.assert_array_equal(getattr(got[0], k), getattr(other, k), err_msg=k)
     assert us[0] <= 1.6 * min(us[1:])
+
+
+def _k5_us(tr, ev, schedule):
+    """Median time of the tracklet pass under a schedule, us."""
+    import torch
+    y, z = torch.from_numpy(ev.y).cuda(), torch.from_numpy(ev.z).cuda()
+    tr.set_knobs(schedule=schedule)
+    tr.set_timing(passes=("tracklets",))
+    t = []
+    for _ in range(11):
+        rid = tr.submit(y, z, ev.row_offsets, ev.sector_z_lo, ev.sector_z_hi)
+        tr.get_device(rid)
+        t.append(1e3 * tr.pass_times()["tracklets"])
+        tr.release(rid)
+    return float(np.median(t))
+
+
+@pytest.mark.parametrize("size, sectors, others", [(100, 100, 0), (100, 400, 0), (30, 700, 0), (100, 200, 4)])
+def test_a_full_sector_among_small_ones_is_swept_at_once(size, sectors, others):
+    """One full sector, the others empty or of a few tracks: its tracklets run side by side, so the tracklet pass takes at
+    most 1.25 times the pipeline's (1.4 to 1.9 times when the lanes of a tracklet were chosen by the whole frame's
+    tracklets, and a full sector's were swept in several rounds)."""
+    import types
+
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2502_09138_amd.tracker import Tracker
+    full, few = synth.single_sector(seed=3, n_tracks=size), synth.single_sector(seed=3, n_tracks=max(1, others))
+    counts, y, z = np.zeros((sectors, synth.N_ROWS), np.int64), [], []
+    for s in range(sectors):
+        e = full if s == sectors // 2 else few if others else None
+        if e is not None:
+            counts[s] = np.diff(e.row_offsets.astype(np.int64))
+            y.append(e.y)
+            z.append(e.z)
+    ev = types.SimpleNamespace(y=np.concatenate(y), z=np.concatenate(z), n_sectors=sectors,
+                               row_offsets=np.concatenate([[0], np.cumsum(counts)]).astype(np.uint32),
+                               sector_z_lo=np.full(sectors, full.sector_z_lo[0], np.float32),
+                               sector_z_hi=np.full(sectors, full.sector_z_hi[0], np.float32))
+    ev.n_clusters = len(ev.y)
+    print("case: full sector", size, sectors, others, "N=", ev.n_clusters, flush=True)
+    tr = Tracker(default_config(), max_clusters=ev.n_clusters, max_sectors=sectors)
+    got = []
+    for schedule in (0, 1):
+        tr.set_knobs(schedule=schedule)
+        got.append(tr.track_event(ev, host=True))
+    us = [_k5_us(tr, ev, s) for s in (0, 1)]
+    tr.close()
+    print("tracklets", got[0].n_tracklets, "us: automatic %.0f, pipeline %.0f" % tuple(us), flush=True)
+    for k in FIELDS:
+        np.testing.assert_array_equal(getattr(got[0], k), getattr(got[1], k), err_msg=k)
+    assert us[0] <= 1.25 * us[1]
