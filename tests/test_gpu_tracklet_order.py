@@ -120,28 +120,36 @@ def test_row_by_row_lanes_change_nothing(sectors, primaries, n_min, n_max, stage
         np.testing.assert_array_equal(getattr(got[0], k), getattr(got[1], k), err_msg=k)
 
 
-@pytest.mark.parametrize("kind, size, lanes", [("lone", 30, 16), ("lone", 100, 16), ("pp", 1, 8), ("pp", 2, 4)])
+@pytest.mark.parametrize("kind, size, lanes", [("one", 30, 16), ("one", 100, 16), ("pp", 1, 8), ("pp", 2, 4), ("pp", 4, 2),
+                                               ("short", 600, 2)])
 def test_resident_columns_read_by_other_lanes(kind, size, lanes):
     """The row -> hit column of a resident tracklet is written by one of its lanes and read by all of them, through every
-    number of lanes, and taken over by the next tracklet of the same lanes (one full sector among empty ones has more
-    tracklets than its workgroups hold at once): the columns and results of the lane-per-tracklet pipeline, bit for bit."""
+    number of lanes, and taken over by the next tracklet of the same lanes (short: one sector of 360 chains of three
+    hits, more than its two workgroups hold at once): the columns and results of the lane-per-tracklet pipeline, bit for
+    bit."""
     import types
 
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2502_09138_amd import tracker as T
+    cfg = default_config()
     if kind == "pp":
         ev = synth.pp_time_frame(seed=54, n_orbits=size)
+    elif kind == "one":
+        ev = synth.single_sector(seed=3, n_tracks=size)
     else:
-        one, S, at = synth.single_sector(seed=3, n_tracks=size), 400, 399
-        off = np.zeros(S * synth.N_ROWS + 1, np.uint32)
-        off[at * synth.N_ROWS:(at + 1) * synth.N_ROWS + 1] = one.row_offsets
-        ev = types.SimpleNamespace(y=one.y, z=one.z, row_offsets=off, n_clusters=one.n_clusters, n_sectors=S,
-                                   sector_z_lo=np.full(S, one.sector_z_lo[0], np.float32),
-                                   sector_z_hi=np.full(S, one.sector_z_hi[0], np.float32))
+        cfg = default_config(min_tracklet_hits=3, min_track_hits=3)
+        R, S, at = synth.N_ROWS, size, size - 1
+        y = np.array([[y + 5.0 * (r // 5 % 2) - 2.5 for y in (-8.0, 0.0, 8.0) for z in range(4)] for r in range(R)])
+        z = np.array([[20.0 + 20.0 * z + 0.01 * r for y in range(3) for z in range(4)] for r in range(R)])
+        off = np.zeros(S * R + 1, np.uint32)
+        off[at * R:(at + 1) * R + 1] = np.arange(0, y.size + 1, 12)
+        ev = types.SimpleNamespace(y=y.astype(np.float32).ravel(), z=z.astype(np.float32).ravel(), row_offsets=off,
+                                   n_clusters=y.size, n_sectors=S, sector_z_lo=np.zeros(S, np.float32),
+                                   sector_z_hi=np.full(S, 250.0, np.float32))
     print("case: resident columns", kind, size, "N=", ev.n_clusters, flush=True)
-    tr = T.Tracker(default_config(), max_clusters=ev.n_clusters, max_sectors=ev.n_sectors)
+    tr = T.Tracker(cfg, max_clusters=ev.n_clusters, max_sectors=ev.n_sectors, max_tracklets=ev.n_clusters)
     got = []
     for schedule in (2, 1):
         tr.set_knobs(schedule=schedule)
@@ -152,9 +160,12 @@ def test_resident_columns_read_by_other_lanes(kind, size, lanes):
         held = (info[0] > 0) & (row >= info[1]) & (row <= info[2])
         got.append((out, np.where(info[0] > 0, info, 0), np.where(held, col, -2)))
     tr.close()
-    n = got[0][0].n_tracklets
-    assert next(v for v in (16, 8, 4, 2) if v == 2 or n * v <= 49152) == lanes
-    assert got[1][0].n_tracklets == n > (7 * 16 if size == 100 else 0)
+    n, parts = got[0][0].n_tracklets, (768 + ev.n_sectors - 1) // ev.n_sectors
+    if kind == "short":
+        assert n > 128 * parts
+    else:
+        assert next(v for v in (16, 8, 4, 2) if v == 2 or n * v <= 49152) == lanes
+    assert got[1][0].n_tracklets == n and got[0][0].n_tracks > 0
     for k in FIELDS:
         np.testing.assert_array_equal(getattr(got[0][0], k), getattr(got[1][0], k), err_msg=k)
     for a, b in zip(got[0][1:], got[1][1:]):
