@@ -308,7 +308,9 @@ __device__ __forceinline__ int32_t search(const DevPtrs& d, uint32_t sr, const R
 // starts, its window is read with lane permutes, and the winner comes from an LDS minimum over (deviation, position): the
 // smallest deviation, ties to the smaller position, which is what the ascending scan of search_m takes.
 // k_up and k_down: 32-orbit frame 2151 -> 1843 us, 512 uneven chunks 5466 -> 5010, 8 heavy-ion orbits 924 -> 833.  Items of 2:
-// +4%, of 6: +2%.  A window of more than two runs (a narrow grid under a wide cap) is left to search_m.
+// +4%, of 6: +2%.  A window of more than two runs (a narrow grid under a wide cap) is left to search_m, and the wave's other
+// windows with it: shared after it, they made a central event with a gate of 40 sigma and a cap of 15 cm 2215 us instead of
+// 1815 (2040 lane by lane throughout).
 constexpr int kItem = 4;
 struct WaveSearch {
   unsigned long long key[kThreads];   // per lane: (deviation, position) of its best candidate
@@ -376,13 +378,12 @@ __device__ __forceinline__ int32_t search_wave(const DevPtrs& d, const Row& row,
     e = meta.x + (uint32_t)iz1 * ny + (uint32_t)iy1;
     b1 = ny <= (uint32_t)kRunBins ? e : b0 + (uint32_t)(iy1 - iy0);
   }
+  // some lane has more than two runs: it would search alone, so all do, beside it
+  if (__any(want && b1 + ny < e)) return want ? search_m(d, meta, rk, sc, t, k, zref, hv) : -1;
   l.key[lane] = ~0ull;
-  int32_t alone = -1;
-  const bool far = want && b1 + ny < e;
-  if (far) alone = search_m(d, meta, rk, sc, t, k, zref, hv);   // more than two runs
   // up to two runs per lane: [q0, h0) and [q1, h1)
   uint32_t q0 = 0, h0 = 0, q1 = 0, h1 = 0;
-  if (want && !far) {
+  if (want) {
     q0 = row.start(b0);
     h0 = row.start(b1 + 1);
     if (b1 < e) {
@@ -453,7 +454,7 @@ __device__ __forceinline__ int32_t search_wave(const DevPtrs& d, const Row& row,
   }
   wave_lds_order();
   const unsigned long long best = l.key[lane];
-  if (best == ~0ull) return alone;
+  if (best == ~0ull) return -1;
   hv = l.hv[lane];
   return (int32_t)(uint32_t)best;
 }
