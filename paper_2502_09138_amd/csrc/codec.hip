@@ -147,6 +147,20 @@ __global__ void __launch_bounds__(kThreads) k_codec_models(CodecArgs a) {
   }
   const uint32_t sr = blockIdx.x;
   const uint32_t b = a.row_off[sr], n = a.row_off[sr + 1] - b, words = (n + 31) / 32;
+  if (n <= (uint32_t)kWave) {   // by its first wave, without barriers (see emit_row)
+    const uint32_t p = threadIdx.x;
+    if (p >= (uint32_t)kWave) return;
+    const uint32_t key = p < n ? a.W[b + p] : 0u, id = p < n ? a.sid[b + p] - b : 0u;
+    const bool un = p < n && !(key && (a.tk_pack[0x7FFFFFu - (key & 0x7FFFFFu)] & 1ull));
+    if (p < 2) bits[p] = 0u;
+    wave_lds_order();
+    if (un) atomicOr(&bits[id / 32], 1u << (id % 32));
+    wave_lds_order();
+    if (p < (n + 7) / 8) a.un_bits[b + p] = (uint8_t)(bits[p / 4] >> (8 * (p % 4)));
+    const uint32_t total = (uint32_t)__popcll(__ballot(un));
+    if (p == 0) a.row_cnt[sr] = total;
+    return;
+  }
   for (uint32_t w = threadIdx.x; w < words; w += kThreads) bits[w] = 0u;
   __syncthreads();
   constexpr int kU = 4;
@@ -175,10 +189,23 @@ __global__ void __launch_bounds__(kThreads) k_codec_models(CodecArgs a) {
   if (threadIdx.x == 0) a.row_cnt[sr] = total;
 }
 
-// The raw list of row sr, in input order.
+// The raw list of row sr, in input order.  Rows of up to 64 clusters are listed by one wave (and marked by one, above): a
+// // request of many small sectors is bound by its rows, of which a CU then holds two to three times as many (2000 sectors of 700
+// clusters, 304k rows: the call 660 -> 365 us, 540 when the tracks' clusters were marked in a word per cluster).
 __device__ __forceinline__ void emit_row(const CodecArgs& a, uint32_t sr, uint32_t* wsum) {
   const uint32_t b = a.row_off[sr], n = a.row_off[sr + 1] - b, bytes = (n + 7) / 8;
   uint32_t base = a.row_pos[sr];
+  if (n <= (uint32_t)kWave) {
+    const uint32_t p = threadIdx.x;
+    if (p >= (uint32_t)kWave) return;
+    const bool un = p < n && (a.un_bits[b + p / 8] >> (p % 8) & 1u);
+    const uint32_t k = base + (uint32_t)__popcll(__ballot(un) & ((1ull << p) - 1ull));
+    if (un) {
+      a.un_row[k] = (uint8_t)(sr % a.R);
+      reinterpret_cast<float2*>(a.un_yz)[k] = make_float2(a.y[b + p], a.z[b + p]);
+    }
+    return;
+  }
   for (uint32_t w0 = 0; w0 < bytes; w0 += kThreads) {   // block-uniform chunks
     const uint32_t w = w0 + threadIdx.x;
     uint32_t v = w < bytes ? a.un_bits[b + w] : 0u, total;

@@ -51,6 +51,13 @@ __device__ __forceinline__ T wave_inclusive_scan(T x) {
   return x;
 }
 
+// LDS accesses of a wave complete in order; keeps the compiler to it.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Block exclusive scan of one value per thread.  `wsum` is LDS scratch of
 // blockDim/64 entries.  Returns the exclusive prefix; *total receives the sum.
 template <typename T>

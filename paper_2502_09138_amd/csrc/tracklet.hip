@@ -319,11 +319,6 @@ struct WaveSearch {
 };
 static_assert(kItem % 2 == 0 && kItem <= kGroup, "items are loaded in pairs; the arrays' slack covers a group");
 
-__device__ __forceinline__ void wave_lds_order() {   // LDS accesses of a wave complete in order; keep the compiler to it
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 template <int kCtrl, int kRows, class Op>
 __device__ __forceinline__ uint32_t dpp_step(uint32_t v, Op op) {
   return op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRows, 0xF, false));

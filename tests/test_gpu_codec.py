@@ -183,3 +183,41 @@ def test_merge_and_encode_leave_the_intermediates(torch_cuda):
     assert [k for k in arrays if not np.array_equal(before[k], after[k])] == []
     for k in first:
         assert np.array_equal(first[k].cpu().numpy(), again[k].cpu().numpy()), k
+
+
+@pytest.mark.parametrize("n_tracks", [2, 45, 60, 100])
+def test_codec_rows_of_about_a_wave(torch_cuda, n_tracks):
+    """Rows listed by one wave (up to 64 clusters) and by a workgroup, empty ones among them."""
+    ev = synth.single_sector(seed=3, n_tracks=n_tracks)
+    n = np.diff(ev.row_offsets.astype(np.int64))
+    print("case: single_sector n_tracks", n_tracks, "rows of", n.min(), "to", n.max(), flush=True)
+    assert n_tracks != 60 or (n.min() < 64 < n.max() and (n == 64).any())
+    _run(ev, 0.01, 0.015, "rows of about a wave")
+
+
+def test_encoding_many_small_rows_costs_few_rows(torch_cuda):
+    """2000 sectors of 700 clusters against a central event of as many: an encoding takes at most 4.5 times as long (3.4 to
+    3.6 with a mark per cluster, 5.7 when every row took a workgroup's barriers)."""
+    import time
+    import types
+    from paper_2502_09138_amd.tracker import Tracker
+    one, S = synth.single_sector(seed=3, n_tracks=5), 2000
+    off = np.concatenate([[0], np.cumsum(np.tile(np.diff(one.row_offsets.astype(np.int64)), S))]).astype(np.uint32)
+    many = types.SimpleNamespace(y=np.tile(one.y, S), z=np.tile(one.z, S), n_clusters=S * one.n_clusters, n_sectors=S,
+                                 row_offsets=off, sector_z_lo=np.tile(one.sector_z_lo, S), sector_z_hi=np.tile(one.sector_z_hi, S))
+    us = []
+    for ev in (many, synth.central_event(seed=2)):
+        print("case: encode, time", ev.n_sectors, "sectors N=", ev.n_clusters, flush=True)
+        tr = Tracker(default_config(), max_clusters=ev.n_clusters, max_sectors=ev.n_sectors)
+        rid = tr.submit(ev.y, ev.z, ev.row_offsets, ev.sector_z_lo, ev.sector_z_hi, host=True)
+        tr.get_device(rid)
+        t = []
+        for _ in range(15):
+            a = time.perf_counter()
+            tr.encode(rid, 0.01, 0.015)
+            t.append(1e6 * (time.perf_counter() - a))
+        tr.release(rid)
+        tr.close()
+        us.append(float(np.median(t)))
+    print("encode us: small rows %.0f, central event %.0f, ratio %.2f" % (us[0], us[1], us[0] / us[1]), flush=True)
+    assert us[0] <= 4.5 * us[1]
