@@ -499,8 +499,8 @@ __global__ void __launch_bounds__(kWave) k_merge_refit(DevPtrs d, MergeArgs m) {
 }  // namespace
 
 void launch_merge(const DevPtrs& d, const MergeArgs& m, uint32_t nt, hipStream_t s) {
-  hipLaunchKernelGGL(k_merge_prep, dim3(d.S), dim3(kPrepThreads), 0, s, d, m);
   if (nt == 0) return;
+  hipLaunchKernelGGL(k_merge_prep, dim3(d.S), dim3(kPrepThreads), 0, s, d, m);
   const uint32_t g = (nt + kThreads - 1) / kThreads;
   const uint32_t waves = kThreads / kWave;
   hipLaunchKernelGGL(k_merge_match, dim3((nt + kMatchWaves - 1) / kMatchWaves), dim3(kMatchWaves * kWave), 0, s, d, m);

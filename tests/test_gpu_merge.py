@@ -224,3 +224,23 @@ def test_merge_links_are_those_of_all_pairs(torch_cuda, n_tracks, windows, at_le
         if len(chain) == 1 or mg["ndf"][c] == -1:
             assert np.array_equal(mg["param"][c], tracks.param[h]) and np.array_equal(mg["cov"][c], tracks.cov[h])
             assert mg["chi2"][c] == tracks.chi2[h]
+
+
+def test_merge_of_a_frame_without_tracks(torch_cuda):
+    """Nothing to link: empty arrays, also after a frame with chains on the same tracker."""
+    from paper_2502_09138_amd.tracker import Tracker
+    ev = synth.boundary_crossers(seed=11, n_tracks=30)
+    few = synth.boundary_crossers(seed=12, n_tracks=1)
+    print("case: merge without tracks N=", ev.n_clusters, flush=True)
+    tr = Tracker(default_config(), max_clusters=ev.n_clusters, max_sectors=3)
+    for e, some in ((ev, True), (few.sector_slice(range(3)), True), (ev, True)):
+        _, mg = tr.track_and_merge(e.y, e.z, e.row_offsets, e.sector_z_lo, e.sector_z_hi, [0, 1, 2], host=True)
+        assert (len(mg["heads"]) > 0) == some
+        # a few clusters of one row: no tracks
+        n = 5
+        off = np.zeros(3 * R + 1, np.uint32)
+        off[40:] = n
+        tracks, mg = tr.track_and_merge(e.y[:n], e.z[:n], off, e.sector_z_lo, e.sector_z_hi, [0, 1, 2], host=True)
+        assert tracks.n_tracks == 0 and mg["first"].tolist() == [0]
+        assert all(len(v) == 0 for k, v in mg.items() if k != "first")
+    tr.close()
