@@ -276,8 +276,8 @@ tpc_status tpc_track_timeframe(tpc_tracker* t, const tpc_timeframe* tf, uint64_t
  * not from the tracker's own workspace, and the call allocates nothing (no
  * hipMalloc, hipFree or allocating library routine).  Frames whose workspace
  * (tpc_workspace_bytes_for their cluster and sector counts) exceeds the array
- * are rejected with TPC_E_INVAL and a message; that is about 0.85M clusters
- * at the default capacities (about 300 B per cluster).  The array is shared by
+ * are rejected with TPC_E_INVAL and a message; that is about 0.74M clusters
+ * at the default capacities (about 360 B per cluster).  The array is shared by
  * every tracker on the device and keeps the last request's contents: requests
  * that overlap on one device race, so issue the next one only after the
  * previous one was released.  Results are read with tpc_get_tracks (host
@@ -469,7 +469,9 @@ tpc_status tpc_set_knob(tpc_tracker* t, int32_t knob, int32_t value);
 #define TPC_TIME_ALL_PASSES 0x3F
 tpc_status tpc_set_timing(tpc_tracker* t, int32_t pass_mask);
 /* Milliseconds of each pass of the last completed request; -1 for a pass
- * that was not timed.  TPC_E_INVAL if timing was off for that request. */
+ * that was not timed.  The last kernel of K6 writes the result header to host
+ * memory itself, so the output pass holds no work: it reads the distance of
+ * two event records.  TPC_E_INVAL if timing was off for that request. */
 tpc_status tpc_get_pass_times(tpc_tracker* t, float* ms, int32_t n);
 
 #ifdef __cplusplus

@@ -16,6 +16,8 @@ HIPCC_FLAGS = [
     # no packed-FP32 instructions in generated code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument",
+    # & of comparisons keeps the searches' tests free of branches
+    "-Wno-bitwise-instead-of-logical",
 ]
 
 

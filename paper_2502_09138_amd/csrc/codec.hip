@@ -38,9 +38,6 @@ constexpr int kPer = 8;                           // track clusters per lane
 constexpr uint32_t kChunk = kPer * kThreads;      // and per workgroup
 constexpr uint32_t kTrackCap = 512;               // track boundaries staged per workgroup
 
-__device__ __forceinline__ uint32_t grid_stride() { return gridDim.x * blockDim.x; }
-__device__ __forceinline__ uint32_t gtid() { return blockIdx.x * blockDim.x + threadIdx.x; }
-
 // Last index k with a[k] <= v in the ascending array a[0..n] (a[0] <= v).
 __device__ __forceinline__ uint32_t last_le(const uint32_t* a, uint32_t n, uint32_t v) {
   uint32_t lo = 0, hi = n;   // a[lo] <= v < a[hi] (a[n] treated as +inf)

@@ -187,7 +187,7 @@ __device__ __forceinline__ int collect(const Staged& row, const Grid& g, float2 
   Walk k = walk_of(row, g, h, wy, wz);
   int n = 0;
   while (next_group(k, row, g.ny, h, wy, wz, [&](uint32_t q, bool pass) {
-    if (pass & n < Sh::kLen) list[n][lane] = (typename Sh::Place)q;
+    if (pass & (n < Sh::kLen)) list[n][lane] = (typename Sh::Place)q;
     n += pass ? 1 : 0;
   })) {
   }
@@ -245,7 +245,7 @@ __device__ __forceinline__ void test_pairs(const Stage<Sh>& S, const Row& dn, co
       for (int k = 0; k < kUp; ++k) {
         const float dev = deviation(h, pd, pu[k], t, rho);
         // lower hits ascend, so of two pairs with the same upper hit the first has the smaller lower one
-        const bool take = kd < nd & u0 + k < nu & (dev < best.dev | (dev == best.dev & qu[k] < best.u));
+        const bool take = (kd < nd) & (u0 + k < nu) & ((dev < best.dev) | ((dev == best.dev) & (qu[k] < best.u)));
         best.dev = take ? dev : best.dev;
         best.u = take ? qu[k] : best.u;
         best.d = take ? qd : best.d;

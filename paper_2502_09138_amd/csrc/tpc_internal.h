@@ -180,7 +180,7 @@ struct CodecArgs {
   uint32_t n_tracks;
   uint64_t n_cl;
   const uint32_t* row_off;     // [SR + 1] input-order row offsets
-  uint32_t SR, R, N;
+  uint32_t SR, R;
   const RowConst* rows;        // [R] (x)
   const float* y;              // [N] input coordinates
   const float* z;

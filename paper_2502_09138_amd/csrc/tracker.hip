@@ -1020,7 +1020,6 @@ tpc_status tpc_encode_tracks(tpc_tracker* t, uint64_t request_id, float q_y, flo
   a.row_off = d.row_off;
   a.SR = t->cur_S * t->caps.R;
   a.R = t->caps.R;
-  a.N = t->cur_N;
   a.rows = d.rows;
   a.y = d.y;
   a.z = d.z;

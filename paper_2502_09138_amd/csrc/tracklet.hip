@@ -108,30 +108,26 @@ __device__ __forceinline__ float asin_over_prime(float u) {
   return (u * frsqrt(1.0f - u2) - asinf(u)) / u2;
 }
 // Helix transport from x to x + dx with covariance; false on |sin phi| >= s_max or |u| >= 1.
-// kNoExit: the failure tests do not branch (the row-synchronous waves, where a
-// branch costs every lane); on false the state then holds meaningless values,
-// and every caller stops the tracklet without reading it again.
+// The failure tests do not branch (a branch costs every lane of the wave); on
+// false the state holds meaningless values, and every caller stops the
+// tracklet without reading it again.
 //
 // The increments of one row step (dy, dz, kappa*dx) and the Jacobian are
 // evaluated in float32: their rounding is relative to the step, far below the
 // tolerance.  They are accumulated into the state in par_t, and the covariance
 // is transported in cov_t.
-template <bool kNoExit>
 __device__ __forceinline__ bool propagate(Trk& t, float dx, const KfConst& k) {
   using V = cov_t;
   const float s1 = float(t.p[2]), tl = float(t.p[3]), qp = float(t.p[4]);
   const float kap = k.bk * qp;
   const par_t s2p = t.p[2] + par_t(kap * dx);
   const float s2 = float(s2p);
-  if (!kNoExit && !(fabsf(s1) < k.s_max)) return false;
-  if (!kNoExit && !(fabsf(s2) < k.s_max)) return false;
   const float c1 = fsqrt((1.0f - s1) * (1.0f + s1));
   const float c2 = fsqrt((1.0f - s2) * (1.0f + s2));
   const float ic = frcp(c1 + c2);
   const float dy = dx * ((s1 + s2) * ic);
   const float L = fsqrt(dx * dx + dy * dy);
   const float u = 0.5f * kap * L;
-  if (!kNoExit && !(fabsf(u) < 1.0f)) return false;
   const bool ok = fabsf(s1) < k.s_max && fabsf(s2) < k.s_max && fabsf(u) < 1.0f;
   const float sgn = dx >= 0.0f ? 1.0f : -1.0f;
   const float S = sgn * L * asin_over(u);
@@ -898,7 +894,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         if (r + 1 < R && r + 1 > rl) mnx = d.row_meta[srb + r + 1];
         ++steps;
         rk = lrows[r];
-        const bool pok = propagate<true>(t, rk.x - xprev, k);
+        const bool pok = propagate(t, rk.x - xprev, k);
         xprev = rk.x;
         failed = chain && !pok;
         on = pok && (chain || !(fabs_(t.p[0]) > rk.half_y + k.margin));
@@ -1043,7 +1039,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
         if (r >= 1) mA = d.row_meta[srb + (uint32_t)r - 1];
         rk = lrows[r];
         ++steps;
-        const bool pok = propagate<true>(t, rk.x - xprev, k);
+        const bool pok = propagate(t, rk.x - xprev, k);
         xprev = rk.x;
         below = (uint32_t)r < r0;
         on = pok && !(below && fabs_(t.p[0]) > rk.half_y + k.margin);
@@ -1358,7 +1354,7 @@ k_tracklets_rs(DevPtrs d, KfConst k) {
       if (up && r > r0) {
         const RowK rk = st.rk;
         steps += chain ? 0u : 1u;
-        const bool pok = propagate<true>(t, rk.x - xprev, k);
+        const bool pok = propagate(t, rk.x - xprev, k);
         xprev = rk.x;
         failed = failed || (!pok && chain);
         go = pok && (chain || fabs_(t.p[0]) <= rk.half_y + k.margin);
@@ -1433,7 +1429,7 @@ k_tracklets_rs(DevPtrs d, KfConst k) {
       if (down && rr < (int32_t)rout) {   // flags, as in the outward sweep
         const RowK rk = st.rk;
         ++steps;
-        const bool pok = propagate<true>(t, rk.x - xprev, k);
+        const bool pok = propagate(t, rk.x - xprev, k);
         xprev = rk.x;
         go = pok && !(below && fabs_(t.p[0]) > rk.half_y + k.margin);
         down = go;
@@ -1668,7 +1664,7 @@ __device__ __forceinline__ uint32_t sweep(const DevPtrs& d, const KfConst& k, co
     if (up && r > r0) {
       const bool chain = r <= rl;
       steps += chain ? 0u : 1u;
-      const bool pok = propagate<true>(t, rk.x - xprev, k);
+      const bool pok = propagate(t, rk.x - xprev, k);
       xprev = rk.x;
       failed = failed || (!pok && chain);
       const bool go = pok && (chain || fabs_(t.p[0]) <= rk.half_y + k.margin);
@@ -1726,7 +1722,7 @@ __device__ __forceinline__ uint32_t sweep(const DevPtrs& d, const KfConst& k, co
     hnext = col[qn * kPer];
     if (down && q < (int32_t)rout) {
       ++steps;
-      const bool pok = propagate<true>(t, rk.x - xprev, k);
+      const bool pok = propagate(t, rk.x - xprev, k);
       xprev = rk.x;
       const bool below = (uint32_t)q < r0;
       const bool go = pok && !(below && fabs_(t.p[0]) > rk.half_y + k.margin);
