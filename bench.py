@@ -50,14 +50,14 @@ PROFILE_SOURCES = (
 )
 PROFILES = {
     "time_frame": {
-        "digests": ("17173b93fe894ebef3414af21e83e25359411bfa", "9376327f84ab69314b3d89e2fbd807306ff31fa6",
-                    "b9c01736632ed5cde0730e9777a6b8663234cc85", "831c9a0cc463abecb232e02f8e38b3ee4492a863",
-                    "e7e0bd5e3bde6e628b9870c1e5f689130b3c0acd"),
+        "digests": ("489671cbfe0fc05418aad68d91df87cecd30a2dd", "2ed40886c9b760f2a045dbdac605029d18b0e633",
+                    "b9c01736632ed5cde0730e9777a6b8663234cc85", "9c495f80551b4c209aedca591f7df1d1a9070867",
+                    "6e433322cf06d68ff07d3e9c2936e2312c6b1745"),
         "knobs": {"schedule": 1, "select_tile_rows": 4, "refit_order": 0, "link_slots": 4, "link_group": -1,
                   "select_threads": 1024},
         # tracklets: k_seed + k_up + k_sort + k_down + k_guard; VALU of k_up and k_down (the rest is < 5%)
-        "traffic_bytes": {"tracklets": 4_716_400_000, "grid": 292_070_000, "neighbours": 182_230_000},
-        "valu_insts": {"tracklets": 868_535_923, "grid": 21_038_144, "neighbours": 156_074_340},
+        "traffic_bytes": {"tracklets": 4_721_860_000, "grid": 292_370_000, "neighbours": 200_380_000},
+        "valu_insts": {"tracklets": 876_551_341, "grid": 21_038_144, "neighbours": 153_947_744},
         "files": "profiles/time_frame_hbm_traffic.md, profiles/time_frame_sq_counters.md",
     },
 }

@@ -218,7 +218,7 @@ __device__ __forceinline__ void emit_row(const CodecArgs& a, uint32_t sr, uint32
 
 // Workgroups [0, row_blocks): the raw lists.  The others: the codes of kChunk
 // track clusters.  On the 32-orbit frame (9.3M track clusters) the encoder's
-// kernels take 229 us (this one 162 us, about half of it the gather of y and z);
+// kernels take 219 us (this one 161 us, about half of it the gather of y and z);
 // 455 us when every cluster searched its track and its row in global memory
 // from any XCD and the tracks' clusters were marked in a word per cluster.
 __global__ void __launch_bounds__(kThreads) k_codec_stream(CodecArgs a, uint32_t row_blocks, uint32_t per) {

@@ -1877,7 +1877,7 @@ hipError_t init_tracklets() {
 
 // Frames of up to kRowSyncHits hits are swept row by row: at 12 hits a tracklet (12 to 24 were seen) the waves of one lane
 // per tracklet are all resident, two on a SIMD.  Up to kRowSyncMaybe they may be, and the device decides on the number of
-// tracklets: both schedules are launched, and one finds nothing to do (8 launches, 20 us, or 2 launches, 8 us).  Larger
+// tracklets: both schedules are launched, and one finds nothing to do (8 launches, 20 to 35 us, or 2 launches, 8 us).  Larger
 // frames go through the pipeline.  us of a call, pipeline / row by row: 4 dense sectors, 0.92M hits 1420 / 1230; 40 chunks
 // of up to 200k, 1.45M 1380 / 1260; 8 heavy-ion orbits, 2.6M, 2008 waves 1228 / 1083 (1130 here); with more waves than are resident, 8
 // dense sectors, 1.86M 1690 / 2090; 9 heavy-ion orbits, 2.9M 1268 / 1530.
@@ -1886,7 +1886,7 @@ hipError_t init_tracklets() {
 // the pipeline's lanes end with their tracklet.  us of K5 on hits without particles, pipeline / row by row (hits a
 // tracklet): 6 sectors of 52k 203 / 625 (2000), 30 of 52k 237 / 631 (2100) and, over less drift, 275 / 346 (148), 36 of 61k 273 / 436
 // (272), 10 of 106k 284 / 308 (238), 8 of 182k 294 / 306 (71); with particles one sector of 142k 792 / 657 (12), of 969k
-// 916 / 795 (65).  Frames whose rows are staged were always swept row by row, and stay so.
+// 916 / 795 (65).  Up to kRowSyncHits, frames whose rows are all staged are swept row by row whatever they hold.
 constexpr uint32_t kResidentWaves = 2048;
 constexpr uint32_t kRowSyncHits = kResidentWaves * kWave * 12;
 constexpr uint32_t kRowSyncMaybe = kResidentWaves * kWave * 24;
